@@ -112,6 +112,9 @@ FullBwdLayout full_bwd_layout(int64_t B, int64_t L, int64_t D, int io) {
     const size_t fused = D % 64 == 0 ? fused_backward_workspace(B, L, D) : 0;
     l.dw = l.scan + align_up(scan > fused ? scan : fused);
     l.total = l.dw + align_up(project_dw_workspace(B * L, D));
+    // The one-kernel backward uses the workspace from its start, and nothing else of it.
+    const size_t fused2 = align_up(fused2_backward_workspace(B, L, D));
+    if (l.total < fused2) l.total = fused2;
     return l;
 }
 
@@ -571,6 +574,16 @@ int recblr_gated_backward(const void* hx, const void* hz, const float* conv_w,
         void* lws = at(ws, lay.full);
         const FullBwdLayout fl = full_bwd_layout(B, L, D, RECBLR_F32);
         void* pack = at(lws, fl.pack);
+        if (fused2_backward_applies(B, L, D, io_of(io), xp, h, dxp, true)) {
+            // One kernel: dhz, dx' whole and the weight gradients.
+            const Fused2BwdArgs fa{xp,  W_r,  b_r, W_i,  b_i,  lambda, h0,   h,       nullptr,
+                                   dhT, dy,   hz,  dhz,  dxp,  dW_r,   db_r, dW_i,    db_i,
+                                   dlambda, dh0, B, L,   D,    io_of(io), lws};
+            if (launch_fused2_backward(fa, strm) != hipSuccess) return RECBLR_ERR_HIP;
+            return status_of(launch_conv_backward(hx, dxp, w4, b4, dhx, dconv_w, dconv_b, K, B,
+                                                  L, D, io_of(io), IoType::kF32, at(ws, lay.conv),
+                                                  strm));
+        }
         if (fused_backward_applies(B, L, D, IoType::kF32, xp, h, pack)) {
             const bool bf = io == RECBLR_BF16;
             void* dzr = at(lws, fl.dzr);
@@ -678,6 +691,12 @@ int recblr_bdlru_backward(const void* x, const void* W_r, const void* b_r, const
     }
     const int64_t M = B * L;
     void* pack = at(ws, lay.pack);
+    if (fused2_backward_applies(B, L, D, io_of(io), x, h, dx, false)) {
+        const Fused2BwdArgs fa{x,    W_r, b_r,     W_i, b_i, lambda, h0,   h,    dh,   dhT,
+                               nullptr, nullptr, nullptr, dx,  dW_r, db_r,   dW_i, db_i, dlambda,
+                               dh0,  B,   L,       D,   io_of(io), ws};
+        return status_of(launch_fused2_backward(fa, strm));
+    }
     if (L > 0 && fused_backward_applies(B, L, D, io_of(io), x, h, pack)) {
         // The scan backward recomputes z on the matrix cores (z never reaches HBM).
         if (launch_pack_groups(W_r, W_i, D, io_of(io), pack, strm) != hipSuccess)

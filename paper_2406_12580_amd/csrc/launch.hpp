@@ -170,6 +170,41 @@ bool fused_backward_applies(int64_t B, int64_t L, int64_t D, IoType io, const vo
 size_t fused_backward_workspace(int64_t B, int64_t L, int64_t D);
 hipError_t launch_fused_backward(const FusedBwdArgs& a, hipStream_t stream);
 
+// Layer backward in one kernel (fused_bwd.hip): z formed again, the adjoint
+// scan, the gate gradients, dx += dz W and dW = dz^T x, with dz kept on chip.
+// x, h, dh and dx of the I/O type, weights and biases too; gated (fp32 only):
+// dh = gy SiLU(gz) on load and dhz stored to gdz.  ws:
+// fused2_backward_workspace bytes, 16-byte aligned.
+struct Fused2BwdArgs {
+    const void* x;
+    const void* wr;
+    const void* br;
+    const void* wi;
+    const void* bi;
+    const float* lambda;
+    const float* h0;
+    const void* h;
+    const void* dh;
+    const float* dhT;
+    const void* gy;
+    const void* gz;
+    void* gdz;
+    void* dx;
+    float* dwr;
+    float* dbr;
+    float* dwi;
+    float* dbi;
+    float* dlambda;
+    float* dh0;
+    int64_t B, L, D;
+    IoType io;
+    void* ws;
+};
+bool fused2_backward_applies(int64_t B, int64_t L, int64_t D, IoType io, const void* x,
+                             const void* h, const void* dx, bool gated);
+size_t fused2_backward_workspace(int64_t B, int64_t L, int64_t D);
+hipError_t launch_fused2_backward(const Fused2BwdArgs& a, hipStream_t stream);
+
 hipError_t launch_scan_forward_serial(const ScanFwdArgs& a, hipStream_t stream);
 hipError_t launch_scan_forward_tree(const ScanFwdArgs& a, hipStream_t stream);
 bool tree_scan_supported(int64_t L);

@@ -264,6 +264,43 @@ def test_full_backward_fused(rb, shape, io):
         assert_close(host(got[k]), want[k], io, k)
 
 
+# The one-kernel layer backward (D = 128): steps at the edges of its 64-step
+# tiles and 32-step blocks, one tile and several, more rows than workgroups.
+ONE_KERNEL_BWD = [(3, 1), (2, 32), (3, 33), (2, 64), (3, 65), (2, 96), (1, 150), (300, 70)]
+
+
+@pytest.mark.parametrize("state", [False, True])
+@pytest.mark.parametrize("io", ["f32", "bf16"])
+@pytest.mark.parametrize("rows", ONE_KERNEL_BWD)
+def test_full_backward_one_kernel(rb, rows, io, state):
+    """Layer and (fp32) gated-layer backward, with and without h0, dL/dh_T and biases."""
+    B, L, D = *rows, 128
+    f = dg.full_inputs(B, L, D, 4700 + B + L, io=io, bias=state, h0=state, grad=True, dhT=state)
+    X, Wr, Wi = (dev(a, io) for a in (f.x, f.Wr, f.Wi))
+    br, bi = (dev(f.br, io), dev(f.bi, io)) if state else (None, None)
+    lam, h0, dhT = dev32(f.lam), dev32(f.h0), dev32(f.dhT)
+    h, _ = rb.bdlru_forward(X, Wr, br, Wi, bi, lam, h0)
+    got = rb.bdlru_backward(X, Wr, br, Wi, bi, lam, h, dev(f.dh, io), h0, dhT)
+    print(f"one-kernel backward {rows} {io} {state}: GPU done", flush=True)
+    want = oracle.backward(f.x, f.Wr, f.br, f.Wi, f.bi, f.lam, f.dh, f.h0, f.dhT)
+    for k in ("dx", "dWr", "dbr", "dWi", "dbi", "dlambda", "dh0"):
+        assert_close(host(got[k]), want[k], io, k)
+    if io == "bf16":
+        return
+    rng = np.random.Generator(np.random.PCG64(4800 + B + L))
+    hz = rng.standard_normal((B, L, D), dtype=np.float32)
+    w = (rng.standard_normal((D, 4)) * 0.5).astype(np.float32)
+    cb = (rng.standard_normal(D) * 0.1).astype(np.float32)
+    args = (dev32(f.x), dev32(hz), dev32(w), dev32(cb), Wr, br, Wi, bi, lam)
+    _, h, _ = rb.gated_forward(*args, h0)
+    got = rb.gated_backward(*args, h, dev32(f.dh), h0, dhT)
+    print(f"one-kernel gated backward {rows} {state}: GPU done", flush=True)
+    want = oracle.gated_backward(f.x, hz, w, cb, f.Wr, f.br, f.Wi, f.bi, f.lam, f.dh, f.h0, f.dhT)
+    for k, v in got.items():
+        if v is not None:
+            assert_close(host(v), want[k], io, k)
+
+
 # (B, D): D % 8 == 0 runs the step fused with the projection (z in registers),
 # with a partial channel block for D = 72; D = 130 takes the two-kernel path.
 @pytest.mark.parametrize("io", ["f32", "bf16"])
