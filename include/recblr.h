@@ -220,10 +220,11 @@ int recblr_bdlru_backward(const void* x, const void* W_r, const void* b_r, const
 /* Full single step: projections of x_t, then one recurrent step
  * (section 3.2 gates, eq:linrnn), z kept on chip.
  *   x : [B][D] io;  h_prev, h_next : [B][D] float (h_next may == h_prev)
- * For bf16 I/O with D in {64, 128, 192, 256} (x, W_r, W_i 16-byte aligned)
- * persistent workgroups keep W_r and W_i in registers and the workspace is
- * not touched; other cases use the workspace of
- * recblr_workspace_size(RECBLR_OP_STEP, ...). */
+ * With D in {64, 128, 192, 256} and x, W_r, W_i 16-byte aligned, few rows
+ * (bf16: up to 2048, fp32: B * D up to 2^20) run as one launch with the weights
+ * spread over the chip, and more bf16 rows as persistent workgroups that keep
+ * W_r and W_i in registers; neither touches the workspace.  Other cases use the
+ * workspace of recblr_workspace_size(RECBLR_OP_STEP, ...). */
 int recblr_bdlru_step(const void* x, const void* W_r, const void* b_r, const void* W_i,
                       const void* b_i, const float* lambda, const float* h_prev, float* h_next,
                       int64_t B, int64_t D, int io, void* ws, size_t ws_bytes, void* stream);

@@ -96,6 +96,13 @@ bool launch_step_resident(const void* x, const void* wr, const void* br, const v
                           float* h_next, int64_t B, int64_t D, IoType io, hipStream_t stream,
                           hipError_t* err);
 
+// The same step for few rows, fp32 or bf16 (D in {64, 128, 192, 256}, x and
+// weights 16-byte aligned): the weights spread over the chip.  Returns false,
+// having launched nothing, where it does not apply or another kernel is faster.
+bool launch_step_few(const void* x, const void* wr, const void* br, const void* wi,
+                     const void* bi, const float* lambda, const float* h_prev, float* h_next,
+                     int64_t B, int64_t D, IoType io, hipStream_t stream, hipError_t* err);
+
 // Scan forward with the gate projections computed per tile on the matrix
 // cores (z never reaches HBM).  Applies when the look-back kernel runs,
 // D % 64 == 0 and x and pack are 16-byte aligned; pack holds the weights

@@ -326,6 +326,154 @@ hipError_t launch_ks(const void* x, const void* wr, const void* br, const void* 
 
 }  // namespace resident
 
+// ----------------------------------------------------------------------------
+// The same step for few rows: what bounds it is the latency of one pass over
+// the weights, not their volume, so they are spread over the chip instead of
+// being held by every workgroup.  A workgroup owns 16 channels and has one wave
+// per 32 inputs: each wave loads its 16 x 32 pieces of W_r and W_i and of x at
+// once, multiplies them (v_mfma_f32_16x16x32_bf16; fp32 operands as the 3-term
+// split hi*hi + hi*lo + lo*hi), and the waves' partial z meet in LDS, added in
+// wave order.  8 rows at D = 256: 2.6 us (bf16; 10.4 us with the weights loaded
+// whole by one workgroup) and 3.2 us (fp32; 16 us with a packing launch).  Then one thread per (row, channel) takes the step; its h_prev, x
+// and constants were loaded before the products.  Row blocks of 16: blockIdx.y,
+// + gridDim.y, ...
+namespace few {
+
+typedef __bf16 b8 __attribute__((ext_vector_type(8)));
+typedef float f4 __attribute__((ext_vector_type(4)));
+
+constexpr int RB = 16;
+
+// 8 consecutive elements as MFMA operand planes (fp32: hi and lo).
+template <typename T>
+struct Frag {
+    static constexpr int P = sizeof(T) == 4 ? 2 : 1;
+    b8 p[P];
+    __device__ __forceinline__ void load(const T* src) {
+        if constexpr (P == 1) {
+            p[0] = *(const b8*)src;
+        } else {
+            typedef float f8 __attribute__((ext_vector_type(8)));
+            const f4 a = *(const f4*)src, c = *(const f4*)(src + 4);
+            const f8 v = {a[0], a[1], a[2], a[3], c[0], c[1], c[2], c[3]};
+            p[0] = __builtin_convertvector(v, b8);
+            p[P - 1] = __builtin_convertvector(v - __builtin_convertvector(p[0], f8), b8);
+        }
+    }
+};
+
+template <typename T>
+__device__ __forceinline__ f4 mma(const Frag<T>& a, const Frag<T>& b) {
+    f4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+    if constexpr (Frag<T>::P == 2) {
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.p[0], b.p[1], acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.p[1], b.p[0], acc, 0, 0, 0);
+    }
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.p[0], b.p[0], acc, 0, 0, 0);
+}
+
+// KS = D / 32 waves.
+template <typename T, int KS>
+__global__ __launch_bounds__(64 * KS) void step_few_kernel(
+    const T* x, const T* wr, const T* wi, const T* br, const T* bi, const float* lam,
+    const float* h_prev, float* h_next, int64_t B) {
+    constexpr int D = 32 * KS, NT = 64 * KS;
+    constexpr int kOut = (RB * 16 + NT - 1) / NT;  // outputs a thread takes
+    __shared__ float zs[KS][2][RB][17];
+    const int tid = threadIdx.x, w = wave_id(), lane = tid & 63;
+    const int fr = lane & 15, fq = lane >> 4;
+    const int c0 = 16 * blockIdx.x;
+    Frag<T> fwr, fwi;
+    const int64_t woff = (int64_t)(c0 + fr) * D + 32 * w + 8 * fq;
+    fwr.load(wr + woff);
+    fwi.load(wi + woff);
+    const int ch = c0 + (tid & 15);  // outputs: channel tid % 16, rows tid / 16, + NT / 16, ...
+    const float lv = lam[ch];
+    const float bzr = br ? to_f32(br[ch]) : 0.0f, bzi = bi ? to_f32(bi[ch]) : 0.0f;
+    for (int64_t blk = blockIdx.y; blk * RB < B; blk += gridDim.y) {
+        const int64_t r0 = blk * RB;
+        const int64_t ra = r0 + fr < B ? r0 + fr : B - 1;  // rows past B repeat the last one
+        Frag<T> fx;
+        fx.load(x + ra * D + 32 * w + 8 * fq);
+        float hp[kOut], xv[kOut];
+#pragma unroll
+        for (int q = 0; q < kOut; ++q) {
+            const int row = (tid + q * NT) >> 4;
+            const int64_t r = r0 + row < B ? r0 + row : B - 1;
+            hp[q] = h_prev[r * D + ch];
+            xv[q] = load(x + r * D + ch);
+        }
+        const f4 zr = mma<T>(fx, fwr), zi = mma<T>(fx, fwi);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {  // accumulator: row 4 (lane / 16) + v, column lane % 16
+            zs[w][0][4 * fq + v][fr] = zr[v];
+            zs[w][1][4 * fq + v][fr] = zi[v];
+        }
+        __syncthreads();
+        const ChannelConst cc = channel_const(lv);
+#pragma unroll
+        for (int q = 0; q < kOut; ++q) {
+            const int row = (tid + q * NT) >> 4;
+            if (row >= RB || r0 + row >= B) continue;
+            float a = bzr, b = bzi;
+#pragma unroll
+            for (int k = 0; k < KS; ++k) {
+                a += zs[k][0][row][tid & 15];
+                b += zs[k][1][row][tid & 15];
+            }
+            float alpha, u;
+            gate_forward(xv[q], a, b, cc, alpha, u);
+            h_next[(r0 + row) * D + ch] = fmaf(alpha, hp[q], u);
+        }
+        __syncthreads();  // zs is reused
+    }
+}
+
+template <typename T, int KS>
+hipError_t launch(const void* x, const void* wr, const void* br, const void* wi, const void* bi,
+                  const float* lam, const float* h_prev, float* h_next, int64_t B,
+                  hipStream_t stream) {
+    const int64_t nblk = (B + RB - 1) / RB;
+    constexpr int64_t kMaxY = 1024 / KS;
+    const dim3 grid(2 * KS, (unsigned)(nblk < kMaxY ? nblk : kMaxY));
+    hipLaunchKernelGGL((step_few_kernel<T, KS>), grid, dim3(64 * KS), 0, stream, (const T*)x,
+                       (const T*)wr, (const T*)wi, (const T*)br, (const T*)bi, lam, h_prev, h_next,
+                       B);
+    return hipGetLastError();
+}
+
+template <typename T>
+hipError_t launch_d(int64_t D, const void* x, const void* wr, const void* br, const void* wi,
+                    const void* bi, const float* lam, const float* h_prev, float* h_next,
+                    int64_t B, hipStream_t stream) {
+    switch (D) {
+        case 64: return launch<T, 2>(x, wr, br, wi, bi, lam, h_prev, h_next, B, stream);
+        case 128: return launch<T, 4>(x, wr, br, wi, bi, lam, h_prev, h_next, B, stream);
+        case 192: return launch<T, 6>(x, wr, br, wi, bi, lam, h_prev, h_next, B, stream);
+        default: return launch<T, 8>(x, wr, br, wi, bi, lam, h_prev, h_next, B, stream);
+    }
+}
+
+}  // namespace few
+
+bool launch_step_few(const void* x, const void* wr, const void* br, const void* wi,
+                     const void* bi, const float* lambda, const float* h_prev, float* h_next,
+                     int64_t B, int64_t D, IoType io, hipStream_t stream, hipError_t* err) {
+    if (B <= 0 || D % 64 != 0 || D < 64 || D > 256 || !aligned16(x) || !aligned16(wr) ||
+        !aligned16(wi))
+        return false;
+    // Where the other kernels catch up (us a step, this one against them): bf16,
+    // the resident kernel: D = 256, B = 8: 2.6 against 10.4, 1024: 5.0 against
+    // 10.7, 4096: 11.6 against 11.5; D = 64, 4096: 3.1 against 3.2.  fp32, packing
+    // and the tile kernel: D = 64, B = 16384: 7.0 against 12.3; D = 128, 4096: 8.6
+    // against 14.4, 16384: 19.7 against 16.1; D = 256, 4096: 18.6 against 19.4.
+    if (io == IoType::kF32 ? B * D > (1 << 20) : B > 2048) return false;
+    *err = io == IoType::kF32
+               ? few::launch_d<float>(D, x, wr, br, wi, bi, lambda, h_prev, h_next, B, stream)
+               : few::launch_d<bf16>(D, x, wr, br, wi, bi, lambda, h_prev, h_next, B, stream);
+    return true;
+}
+
 bool launch_step_resident(const void* x, const void* wr, const void* br, const void* wi,
                           const void* bi, const float* lambda, const float* h_prev,
                           float* h_next, int64_t B, int64_t D, IoType io, hipStream_t stream,

@@ -336,6 +336,25 @@ def test_full_step_resident(rb, shape, bias):
     assert_close(host(got), want, "bf16", "h_next")
 
 
+# Rows around one 16-row block, around the last size that the few-rows kernel
+# takes (bf16: 2048 rows, fp32: 2^20 elements) and the other kernels beyond it.
+@pytest.mark.parametrize("bias", [True, False])
+@pytest.mark.parametrize("io,B,D", [("f32", 1, 64), ("bf16", 1, 256), ("f32", 15, 192),
+                                    ("bf16", 16, 64), ("f32", 17, 256), ("bf16", 17, 192),
+                                    ("bf16", 2048, 128), ("bf16", 2049, 128),
+                                    ("f32", 4096, 256), ("f32", 4097, 256), ("f32", 16384, 64)])
+def test_full_step_few_rows(rb, io, B, D, bias):
+    f = dg.full_inputs(B, 1, D, 4160 + B + D, io=io, bias=bias, h0=True)
+    x = f.x[:, 0]
+    br, bi = (dev(f.br, io), dev(f.bi, io)) if bias else (None, None)
+    h = dev32(f.h0)
+    got = rb.bdlru_step(dev(x, io), dev(f.Wr, io), br, dev(f.Wi, io), bi, dev32(f.lam), h)
+    rb.bdlru_step(dev(x, io), dev(f.Wr, io), br, dev(f.Wi, io), bi, dev32(f.lam), h, out=h)
+    want = oracle.step(x, f.Wr, f.br, f.Wi, f.bi, f.lam, f.h0)
+    assert_close(host(got), want, "f32", "h_next")
+    np.testing.assert_array_equal(host(h), host(got))  # in place
+
+
 @pytest.mark.parametrize("io", ["f32", "bf16"])
 def test_full_step_in_place(rb, io):
     """h_next may be h_prev; two steps in a row match two oracle steps."""
