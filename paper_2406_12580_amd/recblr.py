@@ -132,8 +132,10 @@ def _ptr(t):
 
 
 def _stream(stream=None):
-    s = torch.cuda.current_stream() if stream is None else stream
-    return s.cuda_stream
+    if stream is not None:
+        return stream.cuda_stream
+    # torch.cuda.current_stream().cuda_stream without the Stream object around it
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _on_stream(fn):
@@ -146,9 +148,12 @@ def _on_stream(fn):
     argument nothing changes: torch's current stream is the launch stream.
     """
     sig = inspect.signature(fn)
+    pos = list(sig.parameters).index("stream")
 
     @functools.wraps(fn)
     def wrapper(*args, **kwargs):
+        if len(args) <= pos and kwargs.get("stream") is None:
+            return fn(*args, **kwargs)
         bound = sig.bind(*args, **kwargs)
         s = bound.arguments.get("stream")
         if s is None:
@@ -159,8 +164,11 @@ def _on_stream(fn):
     return wrapper
 
 
+_workspace_size = functools.lru_cache(maxsize=256)(recblr_workspace_size)  # a function of sizes
+
+
 def _workspace(op: int, B: int, L: int, D: int, io: int, device):
-    n = recblr_workspace_size(op, B, L, D, io)
+    n = _workspace_size(op, B, L, D, io)
     if n == 0:
         return None, 0
     return torch.empty(n, dtype=torch.uint8, device=device), n
@@ -169,13 +177,13 @@ def _workspace(op: int, B: int, L: int, D: int, io: int, device):
 def _f32(t, shape, name):
     if t is None:
         return None
-    if t.dtype != torch.float32 or tuple(t.shape) != tuple(shape):
+    if t.dtype != torch.float32 or t.shape != shape:
         raise ValueError(f"{name} must be float32 of shape {tuple(shape)}")
     return t
 
 
 def _io(t, shape, dtype, name):
-    if t.dtype != dtype or tuple(t.shape) != tuple(shape):
+    if t.dtype != dtype or t.shape != shape:
         raise ValueError(f"{name} must be {dtype} of shape {tuple(shape)}")
     return t
 
@@ -188,7 +196,7 @@ def bdlru_scan_forward(x, zr, zi, lam, h0=None, stream=None):
     _io(zr, x.shape, x.dtype, "zr"), _io(zi, x.shape, x.dtype, "zi")
     _f32(lam, (D,), "lambda"), _f32(h0, (B, D), "h0")
     h = torch.empty_like(x)
-    hT = torch.empty((B, D), dtype=torch.float32, device=x.device)
+    hT = x.new_empty((B, D), dtype=torch.float32)
     ws, nws = _workspace(OP_SCAN_FORWARD, B, L, D, io, x.device)
     _check(recblr_bdlru_scan_forward(_ptr(x), _ptr(zr), _ptr(zi), _ptr(lam), _ptr(h0), _ptr(h),
                                      _ptr(hT), B, L, D, io, _ptr(ws), nws, _stream(stream)),
@@ -205,8 +213,8 @@ def bdlru_scan_backward(x, zr, zi, lam, h, dh, h0=None, dhT=None, stream=None):
         _io(t, x.shape, x.dtype, n)
     _f32(lam, (D,), "lambda"), _f32(h0, (B, D), "h0"), _f32(dhT, (B, D), "dhT")
     out = {k: torch.empty_like(x) for k in ("dx", "dzr", "dzi")}
-    out["dlambda"] = torch.empty(D, dtype=torch.float32, device=x.device)
-    out["dh0"] = torch.empty((B, D), dtype=torch.float32, device=x.device)
+    out["dlambda"] = x.new_empty(D, dtype=torch.float32)
+    out["dh0"] = x.new_empty((B, D), dtype=torch.float32)
     ws, nws = _workspace(OP_SCAN_BACKWARD, B, L, D, io, x.device)
     _check(recblr_bdlru_scan_backward(
         _ptr(x), _ptr(zr), _ptr(zi), _ptr(lam), _ptr(h0), _ptr(h), _ptr(dh), _ptr(dhT),
