@@ -469,7 +469,6 @@ int recblr_gated_forward(const void* hx, const void* hz, const float* conv_w,
     hipStream_t strm = (hipStream_t)stream;
     float* w4 = (float*)at(ws, lay.w4);
     float* b4 = (float*)at(ws, lay.b4);
-    if (launch_pack_conv(conv_w, conv_b, K, D, w4, b4, strm) != hipSuccess) return RECBLR_ERR_HIP;
     const FullFwdLayout fl = full_fwd_layout(B, L, D, io);
     char* fws = at(ws, lay.full);
     void* pack = fws + fl.pack;
@@ -479,7 +478,9 @@ int recblr_gated_forward(const void* hx, const void* hz, const float* conv_w,
     // tile); elsewhere once, by a streaming kernel.
     if (L > 0 && fused2_forward_applies(B, L, D, io_of(io), hx, W_r, W_i))
         return status_of(launch_fused2_forward(hx, W_r, b_r, W_i, b_i, lambda, h0, h, hT, hz, y,
-                                               B, L, D, io_of(io), fws + fl.scan, strm, w4, b4));
+                                               B, L, D, io_of(io), fws + fl.scan, strm, conv_w,
+                                               conv_b, K));
+    if (launch_pack_conv(conv_w, conv_b, K, D, w4, b4, strm) != hipSuccess) return RECBLR_ERR_HIP;
     if (launch_conv_silu(hx, w4, b4, xp, B, L, D, io_of(io), io_of(io), strm) != hipSuccess)
         return RECBLR_ERR_HIP;
     if (L > 0 && fused_forward_applies(B, L, D, io_of(io), xp, pack)) {

@@ -82,8 +82,9 @@ struct Params {
     float* hT;        // [B][D] or null
     const void* hz;   // gated: [B][L][D] I/O type
     void* y;          // gated: [B][L][D] I/O type
-    const float* cw4;  // conv on load: taps [4][D] (zero past K); x then holds hx
-    const float* cb4;  // conv on load: bias [D]
+    const float* cw;  // conv on load: taps [D][K]; x then holds hx
+    const float* cb;  // conv on load: bias [D] or null
+    int K;
     int64_t L, D, nch;    // nch = B * D
     int64_t ngroups, nseg;
     unsigned* counters;  // look-back mode: tile-row tickets, one per group
@@ -235,12 +236,13 @@ __device__ __forceinline__ void stage_hx(const T* hx, int64_t b, int64_t L, int6
 // order from the bias, as the streaming conv kernel does.
 template <typename T, int D>
 __device__ __forceinline__ void conv_tile(const char* hxb, const float* taps, char* xt, int64_t t0,
-                                          int tid) {
+                                          int rows, int tid) {
     using CG = ConvGeo<T, D>;
     using G = Geo<T, D>;
     constexpr int V = 16 / (int)sizeof(T);
     constexpr int R = CG::kRpg;
     const int j = tid % CG::kCpr, r0 = (tid / CG::kCpr) * R;
+    if (r0 >= rows) return;  // no step there
     float wt[kConvTaps][V], bv[V];
 #pragma unroll
     for (int v = 0; v < V; ++v) {
@@ -486,8 +488,10 @@ __global__ __launch_bounds__(threads<T>(), 2) void fused_fwd_kernel(Params P) {
 
     if constexpr (CONV) {
         // the taps table, visible after the loop's first barrier
-        for (int i = tid; i < 5 * D; i += NT)
-            taps[i] = i < kConvTaps * D ? P.cw4[i] : P.cb4[i - kConvTaps * D];
+        for (int i = tid; i < 5 * D; i += NT) {
+            const int k = i / D, d = i % D;  // [4][D] (zero past K), then the bias
+            taps[i] = k < kConvTaps ? (k < P.K ? P.cw[d * P.K + k] : 0.0f) : P.cb ? P.cb[d] : 0.0f;
+        }
         stage_hx<T, D>(xg, b, P.L, s_cur * TS, hxbuf0, lane, w);
     } else {
         stage_tile<T, D>(xg, b, P.L, s_cur * TS, xbuf0, tid, w);
@@ -555,8 +559,9 @@ __global__ __launch_bounds__(threads<T>(), 2) void fused_fwd_kernel(Params P) {
         lds_barrier();  // the current tile is in LDS for every wave; the h tile is free
         const int64_t s = s_cur;
         const int64_t t0 = s * TS;
+        const int lim = P.L - t0 < TS ? (int)(P.L - t0) : TS;  // valid rows of the tile
         if constexpr (CONV) {
-            conv_tile<T, D>(hxcur, taps, cur, t0, tid);
+            conv_tile<T, D>(hxcur, taps, cur, t0, lim > 32 ? TS : 32, tid);
             lds_barrier();  // x' is in LDS for every wave; hxcur is free
             if (!kEarly && has_next) stage_hx<T, D>(xg, b, P.L, s_next * TS, hxbuf0, lane, w);
         }
@@ -567,144 +572,149 @@ __global__ __launch_bounds__(threads<T>(), 2) void fused_fwd_kernel(Params P) {
             abuf = planes;
         }
 
-        // ---- z = x W^T for 64 steps x this wave's 32 columns (b comes with the gates)
-        f16v acc[MB];
+        // Only the last tile can hold rows past L (they become the identity): the full
+        // tiles take a path without the per-element masks, and a last tile of at most
+        // 32 steps one without its second block (200 steps: 8 blocks -> 7).
+        auto work = [&](auto mb_tag, auto full_tag) {
+            constexpr int MB = decltype(mb_tag)::value;
+            constexpr bool kFull = decltype(full_tag)::value;
+            // ---- z = x W^T for 64 steps x this wave's 32 columns (b comes with the gates)
+            f16v acc[MB];
 #pragma unroll
-        for (int m = 0; m < MB; ++m)
+            for (int m = 0; m < MB; ++m)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) acc[m][v] = 0.0f;
-        {
-            const int R = lane & 31;
+                for (int v = 0; v < 16; ++v) acc[m][v] = 0.0f;
+            {
+                const int R = lane & 31;
 #pragma unroll
-            for (int kk = 0; kk < G::kKk; ++kk) {
-                const int j = 2 * kk + (lane >> 5);
+                for (int kk = 0; kk < G::kKk; ++kk) {
+                    const int j = 2 * kk + (lane >> 5);
 #pragma unroll
-                for (int m = 0; m < MB; ++m) {
-                    const int r = 32 * m + sigma(R);
-                    const int pos = r * G::kRow16 + ((j ^ swz16(r)) << 4);
-                    const b8 a = *(const b8*)(abuf + pos);
-                    if constexpr (G::kF32) {
-                        const b8 alo = *(const b8*)(abuf + TS * G::kRow16 + pos);
-                        acc[m] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, wl[G::kF32 ? kk : 0],
-                                                                        acc[m], 0, 0, 0);
-                        acc[m] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(alo, wf[kk], acc[m], 0,
-                                                                        0, 0);
+                    for (int m = 0; m < MB; ++m) {
+                        const int r = 32 * m + sigma(R);
+                        const int pos = r * G::kRow16 + ((j ^ swz16(r)) << 4);
+                        const b8 a = *(const b8*)(abuf + pos);
+                        if constexpr (G::kF32) {
+                            const b8 alo = *(const b8*)(abuf + TS * G::kRow16 + pos);
+                            acc[m] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, wl[G::kF32 ? kk : 0],
+                                                                            acc[m], 0, 0, 0);
+                            acc[m] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(alo, wf[kk], acc[m], 0,
+                                                                            0, 0);
+                        }
+                        acc[m] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, wf[kk], acc[m], 0, 0, 0);
                     }
-                    acc[m] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, wf[kk], acc[m], 0, 0, 0);
                 }
             }
-        }
-        // ---- hand every lane z_r and z_i of channel cl at steps 32 m + 8 rho + i
+            // ---- hand every lane z_r and z_i of channel cl at steps 32 m + 8 rho + i
 #pragma unroll
-        for (int m = 0; m < MB; ++m)
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                float zr = acc[m][i], zi = acc[m][i + 8];
-                swap16(zr, zi);
-                acc[m][i] = zr;
-                acc[m][i + 8] = zi;
-            }
-
-        // ---- gates (alpha into acc[m][i], beta' into acc[m][i + 8]) and segments.
-        // Only the last tile can hold rows past L (they become the identity);
-        // the full tiles take a path without the per-element masks.
-        Seg run[MB];
-        const int lim = P.L - t0 < TS ? (int)(P.L - t0) : TS;  // valid rows of the tile
-        auto gates = [&](auto full_tag) {
-            constexpr bool kFull = decltype(full_tag)::value;
-#pragma unroll
-            for (int m = 0; m < MB; ++m) {
-                Seg sg{1.0f, 0.0f};
+            for (int m = 0; m < MB; ++m)
 #pragma unroll
                 for (int i = 0; i < 8; ++i) {
-                    float xv;
-                    if constexpr (sizeof(T) == 2)
-                        xv = __uint_as_float((uint32_t)(*(const uint16_t*)(cur + xoff[i] +
-                                                                           32 * m * G::kRow))
-                                             << 16);
-                    else
-                        xv = *(const float*)(cur + xoff[0] + (32 * m + i) * G::kRow);
-                    float a, u;
-                    gate_forward_biased<sizeof(T) == 4>(xv, acc[m][i], acc[m][i + 8], nbr, nbi,
-                                                        cc, a, u);
-                    if constexpr (!kFull) {
-                        const bool ok = 32 * m + 8 * rho + i < lim;
-                        a = ok ? a : 1.0f;
-                        u = ok ? u : 0.0f;
-                    }
-                    acc[m][i] = a;
-                    acc[m][i + 8] = u;
-                    sg = Seg{a * sg.A, fmaf(a, sg.H, u)};
+                    float zr = acc[m][i], zi = acc[m][i + 8];
+                    swap16(zr, zi);
+                    acc[m][i] = zr;
+                    acc[m][i + 8] = zi;
                 }
-                run[m] = sg;
+
+            // ---- gates (alpha into acc[m][i], beta' into acc[m][i + 8]) and segments
+            Seg run[MB];
+            {
+#pragma unroll
+                for (int m = 0; m < MB; ++m) {
+                    Seg sg{1.0f, 0.0f};
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) {
+                        float xv;
+                        if constexpr (sizeof(T) == 2)
+                            xv = __uint_as_float((uint32_t)(*(const uint16_t*)(cur + xoff[i] +
+                                                                               32 * m * G::kRow))
+                                                 << 16);
+                        else
+                            xv = *(const float*)(cur + xoff[0] + (32 * m + i) * G::kRow);
+                        float a, u;
+                        gate_forward_biased<sizeof(T) == 4>(xv, acc[m][i], acc[m][i + 8], nbr, nbi,
+                                                            cc, a, u);
+                        if constexpr (!kFull) {
+                            const bool ok = 32 * m + 8 * rho + i < lim;
+                            a = ok ? a : 1.0f;
+                            u = ok ? u : 0.0f;
+                        }
+                        acc[m][i] = a;
+                        acc[m][i + 8] = u;
+                        sg = Seg{a * sg.A, fmaf(a, sg.H, u)};
+                    }
+                    run[m] = sg;
+                }
+            }
+            // ---- the four runs of a block: exclusive prefix and block total
+            Seg excl[MB], tot[MB];
+#pragma unroll
+            for (int m = 0; m < MB; ++m) {
+                const Seg p{row_partner(run[m].A, odd), row_partner(run[m].H, odd)};
+                const Seg pair = odd ? compose(run[m], p) : compose(p, run[m]);
+                const Seg e1 = odd ? p : Seg{1.0f, 0.0f};
+                const Seg o{half_partner(pair.A, upper), half_partner(pair.H, upper)};
+                tot[m] = upper ? compose(pair, o) : compose(o, pair);
+                excl[m] = upper ? compose(e1, o) : e1;
+            }
+            Seg tile{1.0f, 0.0f};
+#pragma unroll
+            for (int m = 0; m < MB; ++m) tile = compose(tot[m], tile);
+
+            // ---- carry into the tile
+            float cin;
+            if constexpr (LOOKBACK) {
+                uint64_t* const own = P.states + s * P.nch + chan;
+                const float h0v = P.h0 ? P.h0[chan] : 0.0f;
+                if (s == 0) {
+                    cin = h0v;
+                } else {
+                    if (rho == 0) publish(own, pack_aggregate(tile));
+                    uint64_t wd[kWindow];
+#pragma unroll
+                    for (int j = 0; j < kWindow; ++j) {
+                        const int64_t p = s - 1 - j;
+                        wd[j] = p >= 0 ? peek(P.states + p * P.nch + chan) : pack_inclusive(h0v);
+                    }
+#pragma unroll
+                    for (int j = 0; j < kWindow; ++j) {
+                        const int64_t p = s - 1 - j;
+                        if (p >= 0) wd[j] = wait_ready(P.states + p * P.nch + chan, wd[j], P.status);
+                    }
+                    const int64_t oldest = s - kWindow;
+                    cin = fold_window<kWindow>(wd, P.states + (oldest >= 0 ? oldest : 0) * P.nch + chan,
+                                               P.status);
+                }
+                if (rho == 0) publish(own, pack_inclusive(fmaf(tile.A, cin, tile.H)));
+            } else {
+                cin = carry;
+                carry = fmaf(tile.A, cin, tile.H);
+            }
+            if (s == P.nseg - 1 && rho == 0 && P.hT) P.hT[chan] = fmaf(tile.A, cin, tile.H);
+
+            // ---- h of the lane's steps into the LDS h tile
+            float cm = cin;
+#pragma unroll
+            for (int m = 0; m < MB; ++m) {
+                float hv = fmaf(excl[m].A, cm, excl[m].H);
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    hv = fmaf(acc[m][i], hv, acc[m][i + 8]);
+                    char* dst = hst + (32 * m + 8 * rho + i) * G::kHPitch + (16 * w + cl) * G::kEsz;
+                    if constexpr (sizeof(T) == 4)
+                        *(float*)dst = hv;
+                    else
+                        *(uint16_t*)dst = from_f32<bf16>(hv).bits;
+                }
+                cm = fmaf(tot[m].A, cm, tot[m].H);
             }
         };
         if (lim == TS)
-            gates(std::true_type{});
+            work(std::integral_constant<int, MB>{}, std::true_type{});
+        else if (lim > 32)
+            work(std::integral_constant<int, MB>{}, std::false_type{});
         else
-            gates(std::false_type{});
-        // ---- the four runs of a block: exclusive prefix and block total
-        Seg excl[MB], tot[MB];
-#pragma unroll
-        for (int m = 0; m < MB; ++m) {
-            const Seg p{row_partner(run[m].A, odd), row_partner(run[m].H, odd)};
-            const Seg pair = odd ? compose(run[m], p) : compose(p, run[m]);
-            const Seg e1 = odd ? p : Seg{1.0f, 0.0f};
-            const Seg o{half_partner(pair.A, upper), half_partner(pair.H, upper)};
-            tot[m] = upper ? compose(pair, o) : compose(o, pair);
-            excl[m] = upper ? compose(e1, o) : e1;
-        }
-        Seg tile{1.0f, 0.0f};
-#pragma unroll
-        for (int m = 0; m < MB; ++m) tile = compose(tot[m], tile);
-
-        // ---- carry into the tile
-        float cin;
-        if constexpr (LOOKBACK) {
-            uint64_t* const own = P.states + s * P.nch + chan;
-            const float h0v = P.h0 ? P.h0[chan] : 0.0f;
-            if (s == 0) {
-                cin = h0v;
-            } else {
-                if (rho == 0) publish(own, pack_aggregate(tile));
-                uint64_t wd[kWindow];
-#pragma unroll
-                for (int j = 0; j < kWindow; ++j) {
-                    const int64_t p = s - 1 - j;
-                    wd[j] = p >= 0 ? peek(P.states + p * P.nch + chan) : pack_inclusive(h0v);
-                }
-#pragma unroll
-                for (int j = 0; j < kWindow; ++j) {
-                    const int64_t p = s - 1 - j;
-                    if (p >= 0) wd[j] = wait_ready(P.states + p * P.nch + chan, wd[j], P.status);
-                }
-                const int64_t oldest = s - kWindow;
-                cin = fold_window<kWindow>(wd, P.states + (oldest >= 0 ? oldest : 0) * P.nch + chan,
-                                           P.status);
-            }
-            if (rho == 0) publish(own, pack_inclusive(fmaf(tile.A, cin, tile.H)));
-        } else {
-            cin = carry;
-            carry = fmaf(tile.A, cin, tile.H);
-        }
-        if (s == P.nseg - 1 && rho == 0 && P.hT) P.hT[chan] = fmaf(tile.A, cin, tile.H);
-
-        // ---- h of the lane's steps into the LDS h tile
-        float cm = cin;
-#pragma unroll
-        for (int m = 0; m < MB; ++m) {
-            float hv = fmaf(excl[m].A, cm, excl[m].H);
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                hv = fmaf(acc[m][i], hv, acc[m][i + 8]);
-                char* dst = hst + (32 * m + 8 * rho + i) * G::kHPitch + (16 * w + cl) * G::kEsz;
-                if constexpr (sizeof(T) == 4)
-                    *(float*)dst = hv;
-                else
-                    *(uint16_t*)dst = from_f32<bf16>(hv).bits;
-            }
-            cm = fmaf(tot[m].A, cm, tot[m].H);
-        }
+            work(std::integral_constant<int, 1>{}, std::false_type{});
 
         s_prev = s;
         s_cur = s_next;
@@ -811,9 +821,9 @@ hipError_t launch_fused2_forward(const void* x, const void* wr, const void* br, 
                                  const void* bi, const float* lambda, const float* h0, void* h,
                                  float* hT, const void* hz, void* y, int64_t B, int64_t L,
                                  int64_t D, IoType io, void* ws, hipStream_t stream,
-                                 const float* w4, const float* b4) {
+                                 const float* conv_w, const float* conv_b, int K) {
     const fv2::Plan pl = fv2::plan(B, L, D, fv2::waves_of(io));
-    fv2::Params P{x,  wr,        wi,  br,  bi,  lambda, h0, h, hT, hz, y, w4, b4, L, D, B * D,
+    fv2::Params P{x,  wr,        wi,  br,  bi,  lambda, h0, h, hT, hz, y, conv_w, conv_b, K, L, D, B * D,
                   pl.ngroups, pl.nseg, nullptr, nullptr, nullptr};
     if (pl.lookback) {
         P.status = (unsigned*)((char*)ws + kStatusOffset);
@@ -828,8 +838,8 @@ hipError_t launch_fused2_forward(const void* x, const void* wr, const void* br, 
         if (e != hipSuccess) return e;
     }
     const bool gated = y != nullptr;
-    if (w4 && (!gated || !b4)) return hipErrorInvalidValue;  // conv on load: gated layer only
-    if (w4) {
+    if (conv_w && !gated) return hipErrorInvalidValue;  // conv on load: gated layer only
+    if (conv_w) {
         if (io == IoType::kF32) return fv2::launch_mode<float, 128, true, true>(P, pl, stream);
         if (D == 128) return fv2::launch_mode<bf16, 128, true, true>(P, pl, stream);
         return fv2::launch_mode<bf16, 256, true, true>(P, pl, stream);
