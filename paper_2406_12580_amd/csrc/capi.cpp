@@ -95,7 +95,7 @@ FullFwdLayout full_fwd_layout(int64_t B, int64_t L, int64_t D, int io) {
 }
 
 struct FullBwdLayout {
-    size_t zr, zi, dzr, dzi, pack, scan, dw, total;
+    size_t zr, zi, dzr, dzi, pack, pack_dx, scan, dw, total;
 };
 FullBwdLayout full_bwd_layout(int64_t B, int64_t L, int64_t D, int io) {
     size_t zbytes = align_up((size_t)(B * L * D) * sizeof(float));
@@ -105,7 +105,8 @@ FullBwdLayout full_bwd_layout(int64_t B, int64_t L, int64_t D, int io) {
     l.dzr = 2 * zbytes;
     l.dzi = 3 * zbytes;
     l.pack = 4 * zbytes;
-    l.scan = l.pack + align_up(project_pack_workspace(D, io_of(io)));
+    l.pack_dx = l.pack + align_up(project_pack_workspace(D, io_of(io)));
+    l.scan = l.pack_dx + align_up(project_pack_workspace(D, io_of(io)));
     // The scan part serves either the scan after the projection or the fused
     // kernel (D % 64 == 0), whichever the call takes.
     const size_t scan = scan_backward_workspace(B, L, D, io_of(io));
@@ -425,9 +426,7 @@ int recblr_bdlru_forward(const void* x, const void* W_r, const void* b_r, const 
                                                nullptr, B, L, D, io_of(io), at(ws, lay.scan),
                                                strm));
     if (L > 0 && fused_forward_applies(B, L, D, io_of(io), x, pack)) {
-        hipError_t e = launch_pack_groups(W_r, W_i, D, io_of(io), pack, strm);
-        if (e != hipSuccess) return RECBLR_ERR_HIP;
-        return status_of(launch_fused_forward(x, pack, b_r, b_i, lambda, h0, h, hT, B, L, D,
+        return status_of(launch_fused_forward(x, W_r, W_i, pack, b_r, b_i, lambda, h0, h, hT, B, L, D,
                                               io_of(io), at(ws, lay.scan), strm));
     }
     hipError_t e = launch_project_forward(x, W_r, b_r, W_i, b_i, zr, zi, B * L, D, io_of(io),
@@ -484,9 +483,7 @@ int recblr_gated_forward(const void* hx, const void* hz, const float* conv_w,
     if (launch_conv_silu(hx, w4, b4, xp, B, L, D, io_of(io), io_of(io), strm) != hipSuccess)
         return RECBLR_ERR_HIP;
     if (L > 0 && fused_forward_applies(B, L, D, io_of(io), xp, pack)) {
-        if (launch_pack_groups(W_r, W_i, D, io_of(io), pack, strm) != hipSuccess)
-            return RECBLR_ERR_HIP;
-        return status_of(launch_fused_gated_forward(xp, hz, pack, b_r, b_i, lambda, h0, y, h, hT,
+        return status_of(launch_fused_gated_forward(xp, hz, W_r, W_i, pack, b_r, b_i, lambda, h0, y, h, hT,
                                                     B, L, D, io_of(io), fws + fl.scan, strm));
     }
     // Otherwise the layer forward on x', then the gate.
@@ -593,25 +590,27 @@ int recblr_gated_backward(const void* hx, const void* hz, const float* conv_w,
             // as stored), which measured faster than folding it into the scan;
             // the scan recomputes z from fp32 x' with the weights and biases as
             // given (bf16 weights are one exact operand plane).
-            if ((bf && launch_gate_backward(dy, hz, h, nullptr, dhz, n_el, IoType::kBf16,
-                                            IoType::kBf16, strm) != hipSuccess) ||
-                launch_pack_groups(W_r, W_i, D, io_of(io), pack, strm) != hipSuccess)
+            if (bf && launch_gate_backward(dy, hz, h, nullptr, dhz, n_el, IoType::kBf16,
+                                           IoType::kBf16, strm) != hipSuccess)
                 return RECBLR_ERR_HIP;
-            FusedBwdArgs fa{xp,        pack,      b_r,     b_i,         lambda, h0, h, nullptr,
-                            dhT,       dxp,       (float*)dzr, (float*)dzi, dlambda, dh0,
-                            B,         L,         D,       IoType::kF32, at(lws, fl.scan)};
+            void* pack_dx = at(lws, fl.pack_dx);
+            DlambdaRows dl;
+            FusedBwdArgs fa{xp,  W_r, W_i,         pack, pack_dx, b_r, b_i, lambda,
+                            h0,  h,   nullptr,     dhT,         dxp,     (float*)dzr,
+                            (float*)dzi, dlambda, dh0, B, L, D, IoType::kF32, at(lws, fl.scan)};
             fa.gy = dy;
             fa.gz = hz;
             fa.gdz = bf ? nullptr : dhz;
             fa.h_bf16 = bf;
-            if (launch_fused_backward(fa, strm) != hipSuccess) return RECBLR_ERR_HIP;
+            if (launch_fused_backward(fa, &dl, strm) != hipSuccess) return RECBLR_ERR_HIP;
             // dx' += dz W (for bf16 I/O with the bf16 weights as given: one
             // operand plane), then dW from fp32 x'.
             if (launch_project_backward_data(dzr, dzi, W_r, W_i, dxp, B * L, D,
-                                             bf ? IoType::kBf16 : IoType::kF32, pack, strm,
-                                             bf) != hipSuccess ||
+                                             bf ? IoType::kBf16 : IoType::kF32, pack_dx, strm, bf,
+                                             true) != hipSuccess ||
                 launch_project_backward_weights(dzr, dzi, xp, dW_r, db_r, dW_i, db_i, B * L, D,
-                                                IoType::kF32, at(lws, fl.dw), strm) != hipSuccess)
+                                                IoType::kF32, at(lws, fl.dw), strm,
+                                                dl) != hipSuccess)
                 return RECBLR_ERR_HIP;
             return status_of(launch_conv_backward(hx, dxp, w4, b4, dhx, dconv_w, dconv_b, K, B,
                                                   L, D, io_of(io), IoType::kF32, at(ws, lay.conv),
@@ -698,13 +697,14 @@ int recblr_bdlru_backward(const void* x, const void* W_r, const void* b_r, const
                                dh0,  B,   L,       D,   io_of(io), ws};
         return status_of(launch_fused2_backward(fa, strm));
     }
-    if (L > 0 && fused_backward_applies(B, L, D, io_of(io), x, h, pack)) {
+    void* pack_dx = at(ws, lay.pack_dx);
+    const bool fused = L > 0 && fused_backward_applies(B, L, D, io_of(io), x, h, pack);
+    DlambdaRows dl;
+    if (fused) {
         // The scan backward recomputes z on the matrix cores (z never reaches HBM).
-        if (launch_pack_groups(W_r, W_i, D, io_of(io), pack, strm) != hipSuccess)
-            return RECBLR_ERR_HIP;
-        const FusedBwdArgs fa{x,  pack, b_r, b_i, lambda, h0, h, dh, dhT, dx, (float*)dzr,
+        const FusedBwdArgs fa{x,  W_r, W_i, pack, pack_dx, b_r, b_i, lambda, h0, h, dh, dhT, dx, (float*)dzr,
                               (float*)dzi, dlambda, dh0, B, L, D, io_of(io), at(ws, lay.scan)};
-        e = launch_fused_backward(fa, strm);
+        e = launch_fused_backward(fa, &dl, strm);
     } else {
         e = launch_project_forward(x, W_r, b_r, W_i, b_i, zr, zi, M, D, io_of(io), pack, strm);
         if (e != hipSuccess) return RECBLR_ERR_HIP;
@@ -713,11 +713,11 @@ int recblr_bdlru_backward(const void* x, const void* W_r, const void* b_r, const
         e = launch_scan_backward(a, strm);
     }
     if (e != hipSuccess) return RECBLR_ERR_HIP;
-    e = launch_project_backward_data(dzr, dzi, W_r, W_i, dx, M, D, io_of(io), at(ws, lay.pack),
-                                     strm);
+    e = launch_project_backward_data(dzr, dzi, W_r, W_i, dx, M, D, io_of(io), pack_dx, strm, false,
+                                     fused);
     if (e != hipSuccess) return RECBLR_ERR_HIP;
     e = launch_project_backward_weights(dzr, dzi, x, dW_r, db_r, dW_i, db_i, M, D, io_of(io),
-                                        at(ws, lay.dw), strm);
+                                        at(ws, lay.dw), strm, dl);
     return status_of(e);
 }
 

@@ -70,7 +70,7 @@ struct Tile {
 
 // z_r, z_i of the tile for this lane's channel at this wave's 16 steps.
 // x: [B][L][D] (row b is read), pack: [W_r; W_i] of type TW ordered by
-// channel group of 64 (launch_pack_groups), biases (TW) may be null;
+// channel group of 64 (launch_prepare_scan), biases (TW) may be null;
 // D % 64 == 0.  Steps past L read x as zero.  smem: Tile<T, TW>::kSmem
 // bytes, free on entry; all NT threads call this (it holds workgroup
 // barriers).

@@ -500,6 +500,36 @@ __global__ __launch_bounds__(256) void pack_kernel(const T* wr, const T* wi, __b
     if (sizeof(T) == 4) out[total + e] = (__bf16)(v - (float)hi);
 }
 
+// What a scan with the projections fused in needs before it starts, in one
+// launch (each launch costs about 5 us of stream time): the weights ordered by
+// channel group (rows 128 g .. 128 g + 63 are W_r rows of channels 64 g ..
+// 64 g + 63, the next 64 rows the W_i rows of the same channels; D % 64 == 0),
+// for a backward (dx not null) also in the order of the dx product, and the
+// look-back state: n words "not ready", ticket and status 0.
+template <typename T>
+__global__ __launch_bounds__(256) void prepare_kernel(const T* wr, const T* wi, __bf16* groups,
+                                                      __bf16* dx, int64_t D, uint64_t* states,
+                                                      int64_t n, unsigned* ticket) {
+    const int64_t total = 2 * D * D;
+    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    auto put = [&](__bf16* out, float v) {
+        const __bf16 hi = (__bf16)v;
+        out[e] = hi;
+        if (sizeof(T) == 4) out[total + e] = (__bf16)(v - (float)hi);
+    };
+    if (e < total) {
+        const int64_t r = e / D, k = e % D;
+        const int64_t ch = (r / 128) * 64 + r % 64;
+        put(groups, to_f32(((r / 64) % 2 == 0 ? wr : wi)[ch * D + k]));
+        if (dx) {
+            const int64_t in = e / (2 * D), out = e % (2 * D);
+            put(dx, out < D ? to_f32(wr[out * D + in]) : to_f32(wi[(out - D) * D + in]));
+        }
+    }
+    if (e < 2) ticket[e] = 0u;  // ticket, status
+    for (int64_t k = e; k < n; k += (int64_t)gridDim.x * blockDim.x) states[k] = ~0ull;
+}
+
 // Weights ordered by channel group for the scan forward with the projections
 // fused in: rows 128 g .. 128 g + 63 are W_r rows of channels 64 g .. 64 g + 63,
 // the next 64 rows the W_i rows of the same channels (D % 64 == 0).
@@ -1182,30 +1212,36 @@ __global__ __launch_bounds__(256, 2) void step_kernel(const T* x, const __bf16* 
 // its contiguous run of splits in ascending order, then the 8 runs are added
 // in order.  64 consecutive outputs per workgroup keep the reads coalesced.
 constexpr int kRedGroups = 8;
+// With dl.rows > 0 also dLambda = sigmoid(Lambda) * (sum of dl's rows), the same way.
 __global__ __launch_bounds__(64 * kRedGroups) void dw_reduce_kernel(
-    const float* partial, const float* dbpart, int64_t splits, int64_t D, float* dwr, float* dbr,
-    float* dwi, float* dbi) {
-    const int64_t total = 2 * D * D;
+    const float* partial, const float* dbpart, int64_t splits, int64_t D, int64_t total, float* dwr,
+    float* dbr, float* dwi, float* dbi, DlambdaRows dl) {
     const int el = threadIdx.x & 63, g = threadIdx.x >> 6;
     const int64_t e = (int64_t)blockIdx.x * 64 + el;
-    const int64_t per = (splits + kRedGroups - 1) / kRedGroups;
+    const int64_t nb = total > 0 ? total + 2 * D : 0;  // dW and db, then dLambda
+    const bool isl = e >= nb;
+    const int64_t rows = isl ? dl.rows : splits;
+    const int64_t per = (rows + kRedGroups - 1) / kRedGroups;
     const int64_t s0 = g * per;
-    const int64_t s1 = s0 + per < splits ? s0 + per : splits;
+    const int64_t s1 = s0 + per < rows ? s0 + per : rows;
+    const int64_t last = nb + (dl.rows > 0 ? D : 0);
     double s = 0.0;
-    if (e < total + 2 * D) {
-        const float* src = e < total ? partial + e : dbpart + (e - total);
-        const int64_t stride = e < total ? total : 2 * D;
+    if (e < last) {
+        const float* src = isl ? dl.partial + (e - nb) : e < total ? partial + e : dbpart + (e - total);
+        const int64_t stride = isl ? D : e < total ? total : 2 * D;
 #pragma unroll 8
         for (int64_t k = s0; k < s1; ++k) s += (double)src[k * stride];
     }
     __shared__ double red[kRedGroups][64];
     red[g][el] = s;
     __syncthreads();
-    if (g != 0 || e >= total + 2 * D) return;
+    if (g != 0 || e >= last) return;
     double t = red[0][el];
 #pragma unroll
     for (int gg = 1; gg < kRedGroups; ++gg) t += red[gg][el];
-    if (e < total) {
+    if (isl) {
+        dl.dlambda[e - nb] = (float)(t / (1.0 + exp(-(double)dl.lambda[e - nb])));
+    } else if (e < total) {
         const int64_t o = e / D, c = e % D;
         if (o < D) dwr[o * D + c] = (float)t;
         else dwi[(o - D) * D + c] = (float)t;
@@ -1316,13 +1352,16 @@ hipError_t launch_project_forward(const void* x, const void* wr, const void* br,
 
 hipError_t launch_project_backward_data(const void* dzr, const void* dzi, const void* wr,
                                         const void* wi, void* dx, int64_t M, int64_t D,
-                                        IoType io, void* pack, hipStream_t stream, bool dx_f32) {
+                                        IoType io, void* pack, hipStream_t stream, bool dx_f32,
+                                        bool packed) {
     if (M == 0 || D == 0) return hipSuccess;
     dx_f32 = dx_f32 && io == IoType::kBf16;
     const int64_t hoff = pair_offset(dzr, dzi, M * D * 4, fastmm::BM * D * 4);
     if (D % 8 == 0 && hoff >= 0 && aligned16({dzr, dx, pack})) {
-        hipError_t e = launch_pack(wr, wi, D, io, true, pack, stream);
-        if (e != hipSuccess) return e;
+        if (!packed) {
+            hipError_t e = launch_pack(wr, wi, D, io, true, pack, stream);
+            if (e != hipSuccess) return e;
+        }
         const int64_t tiles = ((M + fastmm::BM - 1) / fastmm::BM) *
                               ((D + fastmm::BN - 1) / fastmm::BN);
         if (io == IoType::kF32)
@@ -1354,15 +1393,21 @@ hipError_t launch_project_backward_data(const void* dzr, const void* dzi, const 
     return hipGetLastError();
 }
 
-hipError_t launch_pack_groups(const void* wr, const void* wi, int64_t D, IoType io, void* pack,
-                              hipStream_t stream) {
-    const dim3 grid((unsigned)((2 * D * D + 255) / 256));
+hipError_t launch_prepare_scan(const void* wr, const void* wi, int64_t D, IoType io, void* groups,
+                               void* dx, uint64_t* states, int64_t n, unsigned* ticket,
+                               hipStream_t stream) {
+    const int64_t wb = (2 * D * D + 255) / 256;
+    int64_t sb = (n + 255) / 256;
+    sb = sb > 1024 ? 1024 : sb;
+    const dim3 grid((unsigned)(wb > sb ? wb : sb));
     if (io == IoType::kF32)
-        hipLaunchKernelGGL(fastmm::pack_group_kernel<float>, grid, dim3(256), 0, stream,
-                           (const float*)wr, (const float*)wi, (__bf16*)pack, D);
+        hipLaunchKernelGGL(fastmm::prepare_kernel<float>, grid, dim3(256), 0, stream,
+                           (const float*)wr, (const float*)wi, (__bf16*)groups, (__bf16*)dx, D,
+                           states, n, ticket);
     else
-        hipLaunchKernelGGL(fastmm::pack_group_kernel<bf16>, grid, dim3(256), 0, stream,
-                           (const bf16*)wr, (const bf16*)wi, (__bf16*)pack, D);
+        hipLaunchKernelGGL(fastmm::prepare_kernel<bf16>, grid, dim3(256), 0, stream,
+                           (const bf16*)wr, (const bf16*)wi, (__bf16*)groups, (__bf16*)dx, D,
+                           states, n, ticket);
     return hipGetLastError();
 }
 
@@ -1421,7 +1466,7 @@ size_t project_dw_workspace(int64_t M, int64_t D) {
 hipError_t launch_project_backward_weights(const void* dzr, const void* dzi, const void* x,
                                            float* dwr, float* dbr, float* dwi, float* dbi,
                                            int64_t M, int64_t D, IoType io, void* ws,
-                                           hipStream_t stream) {
+                                           hipStream_t stream, const DlambdaRows& dl) {
     if (D == 0) return hipSuccess;
     const int64_t esz = io == IoType::kF32 ? 4 : 2;
     const int64_t hoff = pair_offset(dzr, dzi, M * D * 4, fastmm::BK * D * 4);
@@ -1443,11 +1488,18 @@ hipError_t launch_project_backward_weights(const void* dzr, const void* dzi, con
                                partial, dbpart, M, D, splits, rows_per_split);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
-        const int64_t total = 2 * D * D + 2 * D;
+        const int64_t total = 2 * D * D + 2 * D + (dl.rows > 0 ? D : 0);
         hipLaunchKernelGGL(fastmm::dw_reduce_kernel, dim3((unsigned)((total + 63) / 64)),
                            dim3(64 * fastmm::kRedGroups), 0, stream, (const float*)partial,
-                           (const float*)dbpart, splits, D, dwr, dbr, dwi, dbi);
+                           (const float*)dbpart, splits, D, 2 * D * D, dwr, dbr, dwi, dbi, dl);
         return hipGetLastError();
+    }
+    if (dl.rows > 0) {
+        hipLaunchKernelGGL(fastmm::dw_reduce_kernel, dim3((unsigned)((D + 63) / 64)),
+                           dim3(64 * fastmm::kRedGroups), 0, stream, (const float*)nullptr,
+                           (const float*)nullptr, (int64_t)0, D, (int64_t)0, dwr, dbr, dwi, dbi, dl);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
     }
     const int64_t splits = project_dw_splits(M, D);
     const int64_t rows_per_split = (M + splits - 1) / splits;

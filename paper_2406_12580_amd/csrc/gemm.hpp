@@ -20,24 +20,39 @@ hipError_t launch_project_forward(const void* x, const void* wr, const void* br,
                                   IoType io, void* pack, hipStream_t stream);
 
 // dx += dz_r W_r + dz_i W_i (dx holds the direct term on entry); dx is in the
-// I/O type, or fp32 when dx_f32 is set.
+// I/O type, or fp32 when dx_f32 is set.  With `packed`, pack already holds the
+// weights in this product's order (launch_prepare_scan).
 hipError_t launch_project_backward_data(const void* dzr, const void* dzi, const void* wr,
                                         const void* wi, void* dx, int64_t M, int64_t D,
                                         IoType io, void* pack, hipStream_t stream,
-                                        bool dx_f32 = false);
+                                        bool dx_f32 = false, bool packed = false);
+
+// Partial rows of dLoss/dq r ([rows][D]) that still have to be summed to
+// dLambda; rows = 0: none.
+struct DlambdaRows {
+    const float* partial = nullptr;
+    int64_t rows = 0;
+    const float* lambda = nullptr;
+    float* dlambda = nullptr;
+};
 
 // dW_r, dW_i = dz^T x and db_r, db_i = column sums of dz; uses
-// project_dw_workspace(M, D) bytes of scratch at `ws`.
+// project_dw_workspace(M, D) bytes of scratch at `ws`.  dl, if it has rows, is
+// summed by the same last launch.
 hipError_t launch_project_backward_weights(const void* dzr, const void* dzi, const void* x,
                                            float* dwr, float* dbr, float* dwi, float* dbi,
                                            int64_t M, int64_t D, IoType io, void* ws,
-                                           hipStream_t stream);
+                                           hipStream_t stream,
+                                           const DlambdaRows& dl = DlambdaRows{});
 
-// Packs [W_r; W_i] by channel group of 64 (rows 128 g.. : W_r rows of the
-// group's channels, then their W_i rows) into project_pack_workspace(D, io)
-// bytes of bf16 planes, for the scan forward with the projections fused in.
-hipError_t launch_pack_groups(const void* wr, const void* wi, int64_t D, IoType io, void* pack,
-                              hipStream_t stream);
+// What the scans with the projections fused in need first, in one launch:
+// [W_r; W_i] by channel group of 64 (rows 128 g.. : W_r rows of the group's
+// channels, then their W_i rows) into `groups`, with dx not null also in the
+// order of launch_project_backward_data (each project_pack_workspace(D, io)
+// bytes of bf16 planes), and the look-back state (n words, ticket, status).
+hipError_t launch_prepare_scan(const void* wr, const void* wi, int64_t D, IoType io, void* groups,
+                               void* dx, uint64_t* states, int64_t n, unsigned* ticket,
+                               hipStream_t stream);
 
 // Recurrent step with the gate projections fused in (z stays in registers):
 // h_next = alpha h_prev + beta x with z = x W^T + b.  Returns false, having

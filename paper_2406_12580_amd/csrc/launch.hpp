@@ -105,15 +105,15 @@ bool launch_step_few(const void* x, const void* wr, const void* br, const void* 
 
 // Scan forward with the gate projections computed per tile on the matrix
 // cores (z never reaches HBM).  Applies when the look-back kernel runs,
-// D % 64 == 0 and x and pack are 16-byte aligned; pack holds the weights
-// ordered by channel group (launch_pack_groups); ws is the scan-forward
-// workspace.
+// D % 64 == 0 and x and pack are 16-byte aligned; pack takes the weights
+// ordered by channel group (project_pack_workspace bytes); ws is the
+// scan-forward workspace.
 bool fused_forward_applies(int64_t B, int64_t L, int64_t D, IoType io, const void* x,
                            const void* pack);
 // Look-back workspace of the fused forward (0 for empty shapes).
 size_t fused_forward_workspace(int64_t B, int64_t L, int64_t D);
-hipError_t launch_fused_forward(const void* x, const void* pack, const void* br, const void* bi,
-                                const float* lambda, const float* h0, void* h, float* hT,
+hipError_t launch_fused_forward(const void* x, const void* wr, const void* wi, void* pack,
+                                const void* br, const void* bi, const float* lambda, const float* h0, void* h, float* hT,
                                 int64_t B, int64_t L, int64_t D, IoType io, void* ws,
                                 hipStream_t stream);
 
@@ -138,12 +138,16 @@ hipError_t launch_fused2_forward(const void* x, const void* wr, const void* br, 
 // the sequence) and the two-tree scan over the power of two >= L with the
 // leading positions as identity (embedding padding), L <= 4096.
 // Layer backward's scan with the gate projections recomputed inside
-// (scan_bwd_fused_kernel): x, weights packed by channel group
-// (launch_pack_groups), biases (may be null); dx in the I/O type, dz_r and
-// dz_i in fp32, [B][L][D].
+// (scan_bwd_fused_kernel): x, the weights and room for them packed by channel
+// group and in the order of launch_project_backward_data
+// (project_pack_workspace bytes each), biases (may be null); dx in the I/O
+// type, dz_r and dz_i in fp32, [B][L][D].
 struct FusedBwdArgs {
     const void* x;
-    const void* pack;
+    const void* wr;
+    const void* wi;
+    void* pack;
+    void* pack_dx;
     const void* br;
     const void* bi;
     const float* lambda;
@@ -176,7 +180,10 @@ struct FusedBwdArgs {
 bool fused_backward_applies(int64_t B, int64_t L, int64_t D, IoType io, const void* x,
                             const void* h, const void* pack);
 size_t fused_backward_workspace(int64_t B, int64_t L, int64_t D);
-hipError_t launch_fused_backward(const FusedBwdArgs& a, hipStream_t stream);
+// *dl: the partial rows of dLambda that the caller's last launch has to sum
+// (launch_project_backward_weights), if any are left.
+struct DlambdaRows;
+hipError_t launch_fused_backward(const FusedBwdArgs& a, DlambdaRows* dl, hipStream_t stream);
 
 // Layer backward in one kernel (fused_bwd.hip): z formed again, the adjoint
 // scan, the gate gradients, dx += dz W and dW = dz^T x, with dz kept on chip.
@@ -259,8 +266,8 @@ hipError_t launch_conv_backward(const void* hx, const void* dxp, const float* w4
                                 hipStream_t stream);
 // The scan forward with the projections fused in (fused_forward_applies) on
 // x = x', storing y = h * SiLU(hz) (and h if not null).
-hipError_t launch_fused_gated_forward(const void* x, const void* hz, const void* pack,
-                                      const void* br, const void* bi, const float* lambda,
+hipError_t launch_fused_gated_forward(const void* x, const void* hz, const void* wr,
+                                      const void* wi, void* pack, const void* br, const void* bi, const float* lambda,
                                       const float* h0, void* y, void* h, float* hT, int64_t B,
                                       int64_t L, int64_t D, IoType io, void* ws,
                                       hipStream_t stream);

@@ -24,6 +24,7 @@
 // nseg-1-r and the forward look-back code applies unchanged.
 #include "device_common.hpp"
 #include "fused_z.hpp"
+#include "gemm.hpp"
 #include "launch.hpp"
 #include "lookback.hpp"
 
@@ -1058,7 +1059,7 @@ size_t fused_backward_workspace(int64_t B, int64_t L, int64_t D) {
     return bwd_layout(B, D, plan_fused_backward(B, L, D)).total;
 }
 
-hipError_t launch_fused_backward(const FusedBwdArgs& a, hipStream_t stream) {
+hipError_t launch_fused_backward(const FusedBwdArgs& a, DlambdaRows* dl, hipStream_t stream) {
     // the output gate is folded into the fp32-x kernels only
     if (a.gy && io_bytes(a.io) != 4) return hipErrorInvalidValue;
     const BwdPlan plan = plan_fused_backward(a.B, a.L, a.D);
@@ -1071,7 +1072,9 @@ hipError_t launch_fused_backward(const FusedBwdArgs& a, hipStream_t stream) {
                       a.dx, a.dzr,   a.dzi,   a.dh0,    partial, a.L, a.D,  a.B * a.D,
                       plan.ngroups, plan.nseg, lookback_ws(ws + lay.lb),
                       counters, dlambda_groups(a.D), a.gy, a.gz, a.gdz};
-    hipError_t e = lookback_reset(P.lb, plan.nseg * P.nch, stream);
+    hipError_t e = launch_prepare_scan(a.wr, a.wi, a.D, a.h_bf16 ? IoType::kBf16 : a.io, a.pack,
+                                       a.pack_dx, P.lb.states, plan.nseg * P.nch, P.lb.ticket,
+                                       stream);
     if (e != hipSuccess) return e;
     const dim3 grid((unsigned)(plan.ngroups * plan.nseg)), block(fusedz::NT);
     const size_t esz = io_bytes(a.io);
@@ -1107,8 +1110,15 @@ hipError_t launch_fused_backward(const FusedBwdArgs& a, hipStream_t stream) {
                                (const bf16*)a.bi);
     }
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    return launch_dlambda(partial, partial2, plan.nseg * a.B, a.D, a.lambda, a.dlambda, counters,
-                          stream);
+    // Few rows of partials: left to the weight gradients' last launch (64 rows a
+    // thread group there); more take the two-stage kernel.
+    const int64_t rows = plan.nseg * a.B;
+    *dl = DlambdaRows{};
+    if (rows <= 512) {
+        *dl = DlambdaRows{partial, rows, a.lambda, a.dlambda};
+        return hipSuccess;
+    }
+    return launch_dlambda(partial, partial2, rows, a.D, a.lambda, a.dlambda, counters, stream);
 }
 
 }  // namespace recblr

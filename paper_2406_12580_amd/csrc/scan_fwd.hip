@@ -27,6 +27,7 @@
 #include "launch.hpp"
 #include "lookback.hpp"
 #include "fused_z.hpp"
+#include "gemm.hpp"
 #include "mfma_tile.hpp"
 
 namespace recblr {
@@ -346,7 +347,7 @@ __device__ __forceinline__ float silu(float c) { return c * sigmoid(c); }
 
 // P.p0 is x; P.p1, P.p2 are unused; P.h may be null for GATED (then only y
 // is stored).  pack: [W_r; W_i] ordered by channel
-// group of 64 (launch_pack_groups); D % 64 == 0.
+// group of 64 (launch_prepare_scan); D % 64 == 0.
 // Occupancy: 3 workgroups per CU for bf16 I/O (LDS 48 KB each, 6 waves per
 // SIMD), 2 for fp32 (its split operands double the staging LDS).
 template <typename T, int K, typename Off, bool GATED>
@@ -635,7 +636,8 @@ size_t fused_forward_workspace(int64_t B, int64_t L, int64_t D) {
 }
 
 template <bool GATED>
-static hipError_t launch_fused_t(const void* x, const void* pack, const void* br, const void* bi,
+static hipError_t launch_fused_t(const void* x, const void* wr, const void* wi, void* pack,
+                                 const void* br, const void* bi,
                                  const float* lambda, const float* h0, void* h, float* hT,
                                  int64_t B, int64_t L, int64_t D, IoType io, void* ws,
                                  const fusedfwd::GatedArgs& G, hipStream_t stream) {
@@ -643,7 +645,8 @@ static hipError_t launch_fused_t(const void* x, const void* pack, const void* br
     const FwdPlan plan = plan_fused(B, L, D);
     FwdParams P{x, nullptr, nullptr, lambda, h0, h, hT, L, D, B * D, plan.ngroups, plan.nseg,
                 lookback_ws(ws)};
-    hipError_t e = lookback_reset(P.lb, plan.nseg * P.nch, stream);
+    hipError_t e = launch_prepare_scan(wr, wi, D, io, pack, nullptr, P.lb.states,
+                                       plan.nseg * P.nch, P.lb.ticket, stream);
     if (e != hipSuccess) return e;
     const dim3 grid((unsigned)(plan.ngroups * plan.nseg)), block(fusedz::NT);
     const bool small = (uint64_t)(B * L * D) * esz < (1ull << 32);
@@ -670,20 +673,20 @@ static hipError_t launch_fused_t(const void* x, const void* pack, const void* br
     return hipGetLastError();
 }
 
-hipError_t launch_fused_forward(const void* x, const void* pack, const void* br, const void* bi,
-                                const float* lambda, const float* h0, void* h, float* hT,
+hipError_t launch_fused_forward(const void* x, const void* wr, const void* wi, void* pack,
+                                const void* br, const void* bi, const float* lambda, const float* h0, void* h, float* hT,
                                 int64_t B, int64_t L, int64_t D, IoType io, void* ws,
                                 hipStream_t stream) {
-    return launch_fused_t<false>(x, pack, br, bi, lambda, h0, h, hT, B, L, D, io, ws,
+    return launch_fused_t<false>(x, wr, wi, pack, br, bi, lambda, h0, h, hT, B, L, D, io, ws,
                                  fusedfwd::GatedArgs{}, stream);
 }
 
-hipError_t launch_fused_gated_forward(const void* x, const void* hz, const void* pack,
-                                      const void* br, const void* bi, const float* lambda,
+hipError_t launch_fused_gated_forward(const void* x, const void* hz, const void* wr,
+                                      const void* wi, void* pack, const void* br, const void* bi, const float* lambda,
                                       const float* h0, void* y, void* h, float* hT, int64_t B,
                                       int64_t L, int64_t D, IoType io, void* ws,
                                       hipStream_t stream) {
-    return launch_fused_t<true>(x, pack, br, bi, lambda, h0, h, hT, B, L, D, io, ws,
+    return launch_fused_t<true>(x, wr, wi, pack, br, bi, lambda, h0, h, hT, B, L, D, io, ws,
                                 fusedfwd::GatedArgs{hz, y}, stream);
 }
 
