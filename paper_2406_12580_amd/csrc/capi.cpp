@@ -559,6 +559,18 @@ int recblr_gated_backward(const void* hx, const void* hz, const float* conv_w,
     void* dh = at(ws, lay.dh);
     void* dxp = at(ws, lay.dxp);
     const int64_t n_el = B * L * D;
+    if (fused2_backward_applies(B, L, D, io_of(io), hx, h, dhx, true)) {
+        // One kernel: dhx, dhz and every parameter gradient.
+        Fused2BwdArgs fa{hx,  W_r,  b_r, W_i, b_i,  lambda, h0,   h,   nullptr, dhT,  dy,  hz,
+                         dhz, dhx,  dW_r, db_r, dW_i, db_i, dlambda, dh0, B,  L,    D,   io_of(io),
+                         at(ws, lay.full)};
+        fa.cw = conv_w;
+        fa.cb = conv_b;
+        fa.dcw = dconv_w;
+        fa.dcb = dconv_b;
+        fa.K = K;
+        return status_of(launch_fused2_backward(fa, strm));
+    }
     if (launch_pack_conv(conv_w, conv_b, K, D, w4, b4, strm) != hipSuccess) return RECBLR_ERR_HIP;
     if (launch_conv_silu(hx, w4, b4, xp, B, L, D, io_of(io), IoType::kF32, strm) != hipSuccess)
         return RECBLR_ERR_HIP;
@@ -572,16 +584,6 @@ int recblr_gated_backward(const void* hx, const void* hz, const float* conv_w,
         void* lws = at(ws, lay.full);
         const FullBwdLayout fl = full_bwd_layout(B, L, D, RECBLR_F32);
         void* pack = at(lws, fl.pack);
-        if (fused2_backward_applies(B, L, D, io_of(io), xp, h, dxp, true)) {
-            // One kernel: dhz, dx' whole and the weight gradients.
-            const Fused2BwdArgs fa{xp,  W_r,  b_r, W_i,  b_i,  lambda, h0,   h,       nullptr,
-                                   dhT, dy,   hz,  dhz,  dxp,  dW_r,   db_r, dW_i,    db_i,
-                                   dlambda, dh0, B, L,   D,    io_of(io), lws};
-            if (launch_fused2_backward(fa, strm) != hipSuccess) return RECBLR_ERR_HIP;
-            return status_of(launch_conv_backward(hx, dxp, w4, b4, dhx, dconv_w, dconv_b, K, B,
-                                                  L, D, io_of(io), IoType::kF32, at(ws, lay.conv),
-                                                  strm));
-        }
         if (fused_backward_applies(B, L, D, IoType::kF32, xp, h, pack)) {
             const bool bf = io == RECBLR_BF16;
             void* dzr = at(lws, fl.dzr);

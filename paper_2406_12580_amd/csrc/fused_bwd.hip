@@ -1,8 +1,11 @@
 // Layer backward in one kernel for D = 128: the gate pre-activations of section
 // 3.2 (z = W x + b) formed again, the adjoint scan of eq:linrnn, the gate
 // gradients, and both projection gradients (dx += dz W and dW = dz^T x), so that
-// neither z nor dz reaches HBM.  It reads x, h and dLoss/dh (or, for the gated
-// layer of Algorithm alg:gated_recurrent, dy and hz), and writes dx (and dhz).
+// neither z nor dz reaches HBM.  It reads x, h and dLoss/dh and writes dx.
+// For the gated layer of Algorithm alg:gated_recurrent (GATE, fp32) it is the
+// whole backward of the core: it reads hx, hz, h and dy, forms x' =
+// SiLU(conv(hx)) and dh = dy SiLU(hz), and writes dhz and, through the conv's
+// transpose, dhx; neither x' nor dx' reaches HBM either.
 //
 // Work decomposition.  A workgroup of 8 waves (one per compute unit) walks
 // whole batch rows from their last step to their first, in tiles of 64 steps x
@@ -20,6 +23,11 @@
 //      straight to memory.  The operand whose contraction index is not
 //      contiguous in LDS is read through the transposing LDS loads.
 //   C  the next tile's x, loaded into registers during B, goes to LDS.
+// With GATE a lane holds one channel's steps in C too (x planes are [channel][step]
+// then, and the operand that needs the transposing reads is the other one): it
+// forms x' from hx and the three steps before, and between B and C it takes its
+// channel's whole dx' from the LDS tile back through the conv, walking the tiles
+// from the end as the adjoint does, so that dc of the three later steps is at hand.
 // Products of two fp32 operands are the 3-term bf16 split of fastmm (hi*hi +
 // hi*lo + lo*hi); bf16 operands are one exact plane.  dW, db and dLambda leave
 // as one fp32 partial per workgroup, summed in double in a fixed order by
@@ -39,7 +47,11 @@
 // again in each tile (kept across the loop they spill: 630 us).  Tiles of 32
 // steps with two tiles in flight, so that one wave of a SIMD is in A while the
 // other is in B, measured 630 us: twice the W traffic, and every stage then
-// waits for loads queued by the one before it.
+// waits for loads queued by the one before it.  The gated backward at
+// 2048 x 200 x 128: 540 us, against 470 us for the same kernel on x' from memory
+// plus 230 us of conv passes around it (and 780 us + 230 us with separate
+// kernels); its loads are spread over B, the conv and z because all at once in
+// flight they spill (595 us).
 #include "device_common.hpp"
 #include "launch.hpp"
 #include "mfma_tile.hpp"
@@ -60,12 +72,12 @@ typedef uint32_t u4v __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) s4 lds_s4;
 
 struct Params {
-    const void* x;        // [B][L][D] TX
+    const void* x;        // [B][L][D] TX: x, or hx (GATE)
     const void* h;        // [B][L][D] TH
     const void* g;        // [B][L][D] TH: dLoss/dh, or dy (GATE)
     const void* gz;       // GATE: hz
     void* gdz;            // GATE: dhz
-    void* dx;             // [B][L][D] TX
+    void* dx;             // [B][L][D] TX: dx, or dhx (GATE)
     const float* h0;      // [B][D] or null
     const float* dhT;     // [B][D] or null
     float* dh0;           // [B][D] or null
@@ -75,8 +87,12 @@ struct Params {
     const void* bi;
     const float* lam;
     float* part_w;        // [gridDim.x][2 D][D]
-    float* part_c;        // [gridDim.x][3][D]: db_r, db_i, sum of dLoss/dq r
+    float* part_c;        // [gridDim.x][kCols][D]: db_r, db_i, sum of dLoss/dq r and
+                          // (GATE) the conv's bias and tap gradients
     int64_t L, B;
+    const float* cw;      // GATE: conv taps [D][K]
+    const float* cb;      // GATE: conv bias [D] or null
+    int K;
 };
 
 // 16-byte chunk permutations of the LDS tiles.  A bf16 row of x (256 bytes)
@@ -149,7 +165,7 @@ __device__ __forceinline__ b8 tr_pair(const char* p0, const char* p1) {
     return __builtin_bit_cast(b8, __builtin_shufflevector(a, c, 0, 1, 2, 3, 4, 5, 6, 7));
 }
 
-template <typename TX, typename TW>
+template <typename TX, typename TW, bool GATE>
 struct Geo {
     static constexpr bool kXf32 = sizeof(TX) == 4;
     static constexpr int PX = kXf32 ? 2 : 1;             // x planes
@@ -157,7 +173,8 @@ struct Geo {
     static constexpr int kXPlane = TS * D * 2;
     static constexpr int kRaw = TS * D * 4;              // fp32 tile: x (fp32 I/O), then dx's direct term
     static constexpr int kDzPlane = 2 * D * TS * 2;
-    static constexpr int kSmem = PX * kXPlane + kRaw + 2 * kDzPlane;
+    static constexpr int kSmem = PX * kXPlane + (GATE ? 2 : 1) * kRaw + 2 * kDzPlane;
+    static constexpr int kCols = GATE ? 3 + 1 + kConvTaps : 3;  // columns of part_c
     static constexpr int kXLoads = TS * D * (int)sizeof(TX) / (NT * 16);  // 16-byte loads a thread
 };
 
@@ -179,13 +196,15 @@ __device__ __forceinline__ f16v mma(const b8 (&a)[PA], const b8 (&b)[PB], f16v a
 
 template <typename TX, typename TH, typename TW, bool GATE>
 __global__ __launch_bounds__(NT, 2) void fused_bwd_kernel(Params P) {
-    using G = Geo<TX, TW>;
+    using G = Geo<TX, TW, GATE>;
     constexpr int PX = G::PX, PW = G::PW;
     constexpr int EX = (int)sizeof(TX), EH = (int)sizeof(TH);
+    static_assert(!GATE || (EX == 4 && EH == 4 && PW == 2), "the gated layer's backward is fp32");
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    char* const xpl = smem;                       // x planes [PX][TS][D]
+    char* const xpl = smem;                       // x planes [PX][TS][D], GATE [PX][D][TS]
     char* const raw = smem + PX * G::kXPlane;     // fp32 [TS][D]: x (fp32 I/O), then dx's direct term
     char* const dzp = raw + G::kRaw;              // dz planes [2][2 D][TS]
+    char* const hxt = dzp + 2 * G::kDzPlane;      // GATE: fp32 [TS][D], hx
 
     const int lane = threadIdx.x & (kWave - 1);
     const int w = wave_id();
@@ -204,11 +223,23 @@ __global__ __launch_bounds__(NT, 2) void fused_bwd_kernel(Params P) {
             for (int v = 0; v < 16; ++v) dw[a][c][v] = 0.0f;
     float nbr, nbi, dbr = 0.0f, dbi = 0.0f, dl = 0.0f, carry = 0.0f;
     ChannelConst cc;
+    // GATE: the lane's channel's taps and bias, their gradients, dc of the three
+    // steps after the tile, hx of the three before it
+    float wt[GATE ? 4 : 1], cbv = 0.0f, dcw[GATE ? 4 : 1], dcb = 0.0f, later[GATE ? 3 : 1],
+        before[GATE ? 3 : 1];
     {
         const int ch = 16 * w + (lane & 15);
         nbr = P.br ? -load((const TW*)P.br + ch) * kLog2e : 0.0f;
         nbi = P.bi ? -load((const TW*)P.bi + ch) * kLog2e : 0.0f;
         cc = channel_const(P.lam[ch]);
+        if constexpr (GATE) {
+            cbv = P.cb ? P.cb[ch] : 0.0f;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                wt[j] = j < P.K ? P.cw[ch * P.K + j] : 0.0f;
+                dcw[j] = 0.0f;
+            }
+        }
     }
 
     // ---- weight fragments from L2 (fragment order: one 16-byte load a lane)
@@ -226,7 +257,8 @@ __global__ __launch_bounds__(NT, 2) void fused_bwd_kernel(Params P) {
     };
 
     // ---- loads of one tile into registers
-    u4v xr[G::kXLoads];
+    u4v xr[GATE ? 1 : G::kXLoads];
+    float hx[GATE ? 2 : 1][GATE ? 8 : 1], hxb[GATE ? 3 : 1];
     float gv[2][8], hp[2][8], zv[GATE ? 2 : 1][GATE ? 8 : 1], ht[GATE ? 2 : 1];
     float h0v, dhTv;  // h_{-1} and dhT where the tile starts or ends its row, else 0
     auto fetch = [&](int64_t b, int s) {
@@ -244,7 +276,7 @@ __global__ __launch_bounds__(NT, 2) void fused_bwd_kernel(Params P) {
         // a thread takes 8 channels (two 16-byte chunks in fp32, one in bf16) of
         // rows 4 w + lane / 16 and 32 + that
 #pragma unroll
-        for (int q = 0; q < 2; ++q) {
+        for (int q = 0; q < (GATE ? 0 : 2); ++q) {
             const uint32_t off = ((t0 + 32 * q + 4 * w + ln / 16) * D + 8 * (ln % 16)) * EX;
 #pragma unroll
             for (int k = 0; k < G::kXLoads / 2; ++k)
@@ -255,26 +287,107 @@ __global__ __launch_bounds__(NT, 2) void fused_bwd_kernel(Params P) {
         for (int m = 0; m < 2; ++m) {
             const uint32_t off = ((t0 + 32 * m + 8 * rho) * D + ch) * EH;
 #pragma unroll
-            for (int i = 0; i < 8; ++i) gv[m][i] = bload<TH>(grs, off + i * D * EH);
+            for (int i = 0; i < (GATE ? 0 : 8); ++i) gv[m][i] = bload<TH>(grs, off + i * D * EH);
             // h_{t-1}: before step 0 the offset wraps past the resource (0)
             hp[m][0] = bload<TH>(hrs, off - D * EH);
 #pragma unroll
             for (int i = 1; i < 8; ++i) hp[m][i] = bload<TH>(hrs, off + (i - 1) * D * EH);
         }
         if constexpr (GATE) {
+#pragma unroll
+            for (int m = 0; m < 2; ++m)
+                ht[m] = bload<TH>(hrs, ((t0 + 32 * m + 8 * rho + 7) * D + ch) * EH);
+        }
+    };
+    // GATE: dy and hz, asked for in the middle of z's products (with the other loads they
+    // spill) and used after r and alpha.
+    auto fetch_g = [&](int64_t b, int s, int ln) {
+        if constexpr (GATE) {
+            const int rho = ln >> 4, ch = 16 * w + (ln & 15);
+            const __amdgpu_buffer_rsrc_t grs = rsrc((const char*)P.g + b * P.L * D * EH, hbytes);
             const __amdgpu_buffer_rsrc_t zrs = rsrc((const char*)P.gz + b * P.L * D * EH, hbytes);
 #pragma unroll
             for (int m = 0; m < 2; ++m) {
-                const uint32_t off = ((t0 + 32 * m + 8 * rho) * D + ch) * EH;
+                const uint32_t off = (((uint32_t)s * TS + 32 * m + 8 * rho) * D + ch) * EH;
 #pragma unroll
-                for (int i = 0; i < 8; ++i) zv[m][i] = bload<TH>(zrs, off + i * D * EH);
-                ht[m] = bload<TH>(hrs, off + 7 * D * EH);
+                for (int i = 0; i < 8; ++i) {
+                    gv[m][i] = bload<TH>(grs, off + i * D * EH);
+                    zv[m][i] = bload<TH>(zrs, off + i * D * EH);
+                }
             }
         }
     };
-    // ---- the loaded x of a tile to LDS: bf16 planes and (fp32) the tile itself
+    // GATE: hx of the lane's channel at its 16 steps, and before the tile.  Asked for
+    // after dx's products, whose registers these loads take (in flight with the others
+    // they spill), and in flight through the conv's backward.
+    auto fetch_hx = [&](int64_t b, int s) {
+        if constexpr (GATE) {
+            const int ln = fresh(lane);
+            const int rho = ln >> 4, ch = 16 * w + (ln & 15);
+            const __amdgpu_buffer_rsrc_t xrs = rsrc((const char*)P.x + b * P.L * D * EX, xbytes);
+            const uint32_t t0 = (uint32_t)s * TS;
+#pragma unroll
+            for (int m = 0; m < 2; ++m) {
+                const uint32_t off = ((t0 + 32 * m + 8 * rho) * D + ch) * EX;
+#pragma unroll
+                for (int i = 0; i < 8; ++i) hx[m][i] = bload<TX>(xrs, off + i * D * EX);
+            }
+#pragma unroll
+            for (int k = 0; k < 3; ++k)  // before step 0 the offset wraps past the resource (0)
+                hxb[k] = bload<TX>(xrs, ((t0 - 3 + k) * D + ch) * EX);
+        }
+    };
+    // ---- the loaded x of a tile to LDS: bf16 planes and (fp32) the tile itself.
+    // GATE: x' = SiLU(conv(hx)) of the lane's channel; the columns of hx and x' that a
+    // wave writes are those that it alone reads.
     auto stage = [&]() {
         const int ln = fresh(lane);
+        if constexpr (GATE) {
+            const int rho = ln >> 4, ch = 16 * w + (ln & 15);
+            char* const hb = hxt + (8 * rho) * (D * 4) + ch * 4;
+#pragma unroll
+            for (int m = 0; m < 2; ++m)
+#pragma unroll
+                for (int i = 0; i < 8; ++i) *(float*)(hb + (32 * m + i) * (D * 4)) = hx[m][i];
+#pragma unroll
+            for (int k = 0; k < 3; ++k) before[k] = hxb[k];
+#pragma unroll
+            for (int m = 0; m < 2; ++m) {
+                float win[11];  // steps 32 m + 8 rho - 3 ..
+#pragma unroll
+                for (int k = 0; k < 3; ++k) {
+                    const int row = 32 * m + 8 * rho - 3 + k;  // before the tile: read row 0
+                    float v = *(const float*)(hxt + (row < 0 ? 0 : row) * (D * 4) + ch * 4);
+                    asm volatile("" : "+v"(v));  // read by every lane, without a branch
+                    win[k] = m == 0 && rho == 0 ? before[k] : v;
+                }
+#pragma unroll
+                for (int i = 0; i < 8; ++i) win[3 + i] = hx[m][i];
+                float xo[8];
+                char* const rbase = raw + (8 * rho) * (D * 4) + (((ch >> 2) ^ (4 * rho)) << 4) +
+                                    (ch & 3) * 4;
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    float c = cbv;
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) c = fmaf(wt[j], win[3 + i - j], c);
+                    xo[i] = c * sigmoid(c);
+                    *(float*)((i < 4 ? rbase : raw + ((rbase - raw) ^ 128)) +
+                              (32 * m + i) * (D * 4)) = xo[i];
+                }
+                u4v hi, lo;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const fastmm::u2v p = fastmm::split2(xo[2 * q], xo[2 * q + 1]);
+                    hi[q] = p.x;
+                    lo[q] = p.y;
+                }
+                char* const dst = xpl + ch * (TS * 2) + ((rho ^ swzdz(ch) ^ (4 * m)) << 4);
+                *(u4v*)dst = hi;
+                *(u4v*)(dst + G::kXPlane) = lo;
+            }
+            return;
+        }
         const int r = 4 * w + ln / 16, jb = ln % 16;
         char* const pos = xpl + r * (D * 2) + ((jb ^ swz16(r)) << 4);
         char* const pr = raw + r * (D * 4) + (((2 * jb) ^ swz32(r)) << 4);
@@ -310,8 +423,14 @@ __global__ __launch_bounds__(NT, 2) void fused_bwd_kernel(Params P) {
         // z
         f16v acc[NB];
         {
+            // x rows (operand rows permuted by sigma) x channels 16 kk + 8 (lane / 32) ..
+            // + 7; GATE: channel rows, 4 steps of sigma's order a lane
             const int r = sigma(ln & 31);
-            const int base = r * (D * 2) + (((ln >> 5) ^ swz16(r)) << 4);
+            const int kr = 8 * (ln >> 5) + ((ln >> 2) & 3);
+            const int base = GATE ? kr * (TS * 2) +
+                                        (((2 * (ln & 1) + ((ln >> 4) & 1)) ^ swzdz(kr)) << 4) +
+                                        4 * (ln & 2)
+                                  : r * (D * 2) + (((ln >> 5) ^ swz16(r)) << 4);
             f16v zero;
 #pragma unroll
             for (int v = 0; v < 16; ++v) zero[v] = 0.0f;
@@ -321,15 +440,36 @@ __global__ __launch_bounds__(NT, 2) void fused_bwd_kernel(Params P) {
                 for (int m = 0; m < NB; ++m) {
                     b8 a[PX];
 #pragma unroll
-                    for (int p = 0; p < PX; ++p)
-                        a[p] = *(const b8*)(xpl + (base ^ (kk << 5)) + m * (32 * D * 2) +
-                                            p * G::kXPlane);
+                    for (int p = 0; p < PX; ++p) {
+                        if constexpr (GATE)
+                            a[p] = tr_pair(xpl + (base ^ (m << 6)) + kk * (16 * TS * 2) +
+                                               p * G::kXPlane,
+                                           xpl + (base ^ (m << 6) ^ 16) + kk * (16 * TS * 2) +
+                                               4 * TS * 2 + p * G::kXPlane);
+                        else
+                            a[p] = *(const b8*)(xpl + (base ^ (kk << 5)) + m * (32 * D * 2) +
+                                                p * G::kXPlane);
+                    }
                     acc[m] = mma<PX, PW>(a, wf[kk & 3], kk == 0 ? zero : acc[m]);
                 }
                 if (kk < 4) load_w(zrs, 8 * w, kk + 4, ln);
-                __builtin_amdgcn_sched_barrier(0x38F);  // the loads stay where they are
+                if (kk == 3) fetch_g(b, s, ln);
+                __builtin_amdgcn_sched_barrier(GATE ? 0 : 0x38F);  // the loads stay where they are
             }
         }
+        // every lane gets z_r and z_i of channel ch at steps 32 m + 8 rho + i; r and alpha
+        float al[NB][8];
+#pragma unroll
+        for (int m = 0; m < NB; ++m)
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                float zr = acc[m][i], zi = acc[m][i + 8];
+                swap16(zr, zi);
+                const float r = fast_rcp(1.0f + fast_exp2(fmaf(zr, -kLog2e, nbr)));
+                acc[m][i] = r;
+                acc[m][i + 8] = zi;
+                al[m][i] = fast_exp2(r * cc.neg_s_l2);
+            }
         // output gate: dh = dy SiLU(hz), dhz = dy h SiLU'(hz)
         if constexpr (GATE) {
             const __amdgpu_buffer_rsrc_t ors = rsrc((char*)P.gdz + b * P.L * D * EH, hbytes);
@@ -346,22 +486,14 @@ __global__ __launch_bounds__(NT, 2) void fused_bwd_kernel(Params P) {
                 }
             }
         }
-        // every lane gets z_r and z_i of channel ch at steps 32 m + 8 rho + i; then r,
-        // alpha and the lane's run (later steps first)
-        float al[NB][8];
+        // the lane's run (later steps first)
         Seg run[NB];
 #pragma unroll
         for (int m = 0; m < NB; ++m) {
             Seg sg{1.0f, 0.0f};
 #pragma unroll
             for (int i = 7; i >= 0; --i) {
-                float zr = acc[m][i], zi = acc[m][i + 8];
-                swap16(zr, zi);
-                const float r = fast_rcp(1.0f + fast_exp2(fmaf(zr, -kLog2e, nbr)));
-                const float a = fast_exp2(r * cc.neg_s_l2);
-                acc[m][i] = r;
-                acc[m][i + 8] = zi;
-                al[m][i] = a;
+                const float a = al[m][i];
                 Seg e{a, a * gv[m][i]};
                 if constexpr (!FULL) {
                     const bool ok = 32 * m + 8 * rho + i < lim;
@@ -456,8 +588,73 @@ __global__ __launch_bounds__(NT, 2) void fused_bwd_kernel(Params P) {
         if (s == 0 && rho == 0 && P.dh0) P.dh0[b * D + ch] = carry;
     };
 
+    // ---- GATE: dx' of the lane's channel (whole, in the fp32 tile) back through the conv:
+    // dc = dx' SiLU'(c), dhx_t = sum_j w_j dc_{t+j}, and the tap and bias gradients
+    auto conv_back = [&](int64_t b, int s, auto full_tag) {
+        constexpr bool FULL = decltype(full_tag)::value;
+        if constexpr (GATE) {
+            const int64_t t0 = (int64_t)s * TS;
+            const int lim = P.L - t0 < TS ? (int)(P.L - t0) : TS;
+            const int ln = fresh(lane);
+            const int rho = ln >> 4, ch = 16 * w + (ln & 15);
+            const __amdgpu_buffer_rsrc_t drs = rsrc((char*)P.dx + b * P.L * D * EX, xbytes);
+            char* const rbase = raw + (8 * rho) * (D * 4) + (((ch >> 2) ^ (4 * rho)) << 4) +
+                                (ch & 3) * 4;
+            const int from = ((ln + 16) & 63) * 4;  // the lane of the next 8 steps
+            if (s == ntiles - 1) later[0] = later[1] = later[2] = 0.0f;
+            float nx[3];
+            float sb = 0.0f, sw[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+            for (int m = 1; m >= 0; --m) {
+                __builtin_amdgcn_sched_barrier(0);
+                float win[11], dc[11];
+#pragma unroll
+                for (int k = 0; k < 11; ++k) {
+                    const int row = 32 * m + 8 * rho - 3 + k;
+                    float v = *(const float*)(hxt + (row < 0 ? 0 : row) * (D * 4) + ch * 4);
+                    asm volatile("" : "+v"(v));  // read by every lane, without a branch
+                    win[k] = k < 3 && m == 0 && rho == 0 ? before[k < 3 ? k : 0] : v;
+                }
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    const float dxv = *(const float*)((i < 4 ? rbase : raw + ((rbase - raw) ^ 128)) +
+                                                      (32 * m + i) * (D * 4));
+                    float c = cbv;
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) c = fmaf(wt[j], win[3 + i - j], c);
+                    const float sg = sigmoid(c);
+                    dc[i] = dxv * (sg * fmaf(c, 1.0f - sg, 1.0f));
+                    if constexpr (!FULL) dc[i] = 32 * m + 8 * rho + i < lim ? dc[i] : 0.0f;
+                    sb += dc[i];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) sw[j] = fmaf(dc[i], win[3 + i - j], sw[j]);
+                }
+                // dc of the three steps after the lane's: the next lane's, across the block
+                // the later block's or tile's first lane's
+#pragma unroll
+                for (int k = 0; k < 3; ++k) {
+                    const float n = __uint_as_float((uint32_t)__builtin_amdgcn_ds_bpermute(
+                        from, (int)__float_as_uint(dc[k])));
+                    dc[8 + k] = rho == 3 ? (m == 1 ? later[k] : nx[k]) : n;
+                    if (m == 1) nx[k] = n;
+                    else later[k] = n;
+                }
+                const uint32_t off = (uint32_t)((t0 + 32 * m + 8 * rho) * D + ch) * EX;
+#pragma unroll
+                for (int i = 0; i < 8; ++i)
+                    bstore<TX>(drs, off + i * D * EX,
+                               fmaf(wt[0], dc[i], fmaf(wt[1], dc[i + 1],
+                                                       fmaf(wt[2], dc[i + 2], wt[3] * dc[i + 3]))));
+            }
+            dcb += sb;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) dcw[j] += sw[j];
+        }
+    };
+
     int s = ntiles - 1;
     fetch(b, s);
+    fetch_hx(b, s);
     stage();
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) load_w(zrs, 8 * w, ks, lane);
@@ -489,7 +686,7 @@ __global__ __launch_bounds__(NT, 2) void fused_bwd_kernel(Params P) {
             for (int ks = 0; ks < 4; ++ks) load_w(prs, 16 * nb + 8 * gate, ks, ln);
         }
         __builtin_amdgcn_sched_barrier(0);
-        if (has_next) fetch(nrow, ns);
+        if (!GATE && has_next) fetch(nrow, ns);
         lds_barrier();
         // ---- dW += dz^T x: rows (outputs) 64 wm + 32 u + lane % 32 at steps 16 ks +
         // 8 (lane / 32) .. + 7, against inputs 64 wn + 32 v + lane % 32 at the same steps
@@ -515,6 +712,13 @@ __global__ __launch_bounds__(NT, 2) void fused_bwd_kernel(Params P) {
                 for (int v = 0; v < 2; ++v)
 #pragma unroll
                     for (int p = 0; p < PX; ++p) {
+                        if constexpr (GATE) {
+                            const int in = 64 * wn + (ln & 31);
+                            const int o = in * (TS * 2) + (((ln >> 5) ^ swzdz(in)) << 4);
+                            c[v][p] = *(const b8*)(xpl + (o ^ (ks << 5)) + v * (32 * TS * 2) +
+                                                   p * G::kXPlane);
+                            continue;
+                        }
                         const int o = bbase ^ (v << 6) ^ ((ks & 1) << 5);
                         c[v][p] = tr_pair(xpl + o + ks * (16 * D * 2) + p * G::kXPlane,
                                           xpl + (o ^ 16) + ks * (16 * D * 2) + 4 * D * 2 +
@@ -573,14 +777,29 @@ __global__ __launch_bounds__(NT, 2) void fused_bwd_kernel(Params P) {
 #pragma unroll
             for (int v = 0; v < 16; ++v) *rp(1 - gate, v) += o[0][v];
             lds_barrier();
-            const uint32_t off = (uint32_t)((t0 + 32 * gate + r0) * D + col) * EX;
+            if constexpr (GATE) {
 #pragma unroll
-            for (int v = 0; v < 16; ++v)
-                bstore<TX>(drs, off + (8 * (v / 4) + (v & 3)) * D * EX,
-                           *rp(gate, v) + o[1][v]);
+                for (int v = 0; v < 16; ++v) *rp(gate, v) += o[1][v];
+            } else {
+                const uint32_t off = (uint32_t)((t0 + 32 * gate + r0) * D + col) * EX;
+#pragma unroll
+                for (int v = 0; v < 16; ++v)
+                    bstore<TX>(drs, off + (8 * (v / 4) + (v & 3)) * D * EX,
+                               *rp(gate, v) + o[1][v]);
+            }
+        }
+        lds_barrier();  // every wave is done with the tile's planes
+        if constexpr (GATE) {
+            if (has_next) {
+                fetch_hx(nrow, ns);
+                fetch(nrow, ns);
+            }
+            if (lim == TS)
+                conv_back(b, s, std::true_type{});
+            else
+                conv_back(b, s, std::false_type{});
         }
         if (!has_next) break;
-        lds_barrier();  // every wave is done with the tile's planes
         stage();
         lds_barrier();
         b = nrow;
@@ -601,7 +820,7 @@ __global__ __launch_bounds__(NT, 2) void fused_bwd_kernel(Params P) {
                 const int col = 64 * wn + 32 * c + (lane & 31);
                 pw[row * D + col] = dw[u][c][v];
             }
-    float* const pc = P.part_c + (int64_t)blockIdx.x * 3 * D;
+    float* const pc = P.part_c + (int64_t)blockIdx.x * G::kCols * D;
     auto fold = [&](float v) {  // the four lanes of a channel, in a fixed order
         const float q = row_partner(v, odd);
         const float two = odd ? q + v : v + q;
@@ -613,6 +832,15 @@ __global__ __launch_bounds__(NT, 2) void fused_bwd_kernel(Params P) {
         pc[ch] = fr;
         pc[D + ch] = fi;
         pc[2 * D + ch] = fl;
+    }
+    if constexpr (GATE) {
+        const float fb = fold(dcb);
+        if (rho == 0) pc[3 * D + ch] = fb;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const float f = fold(dcw[j]);
+            if (rho == 0) pc[(4 + j) * D + ch] = f;
+        }
     }
 }
 
@@ -652,7 +880,8 @@ __global__ __launch_bounds__(256) void reduce_kernel(const float* __restrict__ p
                                                      const float* __restrict__ part_c, int rows,
                                                      const float* __restrict__ lam, float* dwr,
                                                      float* dwi, float* dbr, float* dbi,
-                                                     float* dlambda) {
+                                                     float* dlambda, int cols, float* dcw,
+                                                     float* dcb, int K) {
     typedef float f4 __attribute__((ext_vector_type(4)));
     constexpr int kCols = 16, kGroups = 16;  // 16 x 4 columns a block, 16 row groups
     __shared__ double red[kGroups][kCols * 4];
@@ -661,7 +890,7 @@ __global__ __launch_bounds__(256) void reduce_kernel(const float* __restrict__ p
     const bool isw = blockIdx.x < kWBlocks;
     const int64_t col = ((int64_t)(isw ? blockIdx.x : blockIdx.x - kWBlocks) * kCols + c) * 4;
     const float* src = (isw ? part_w : part_c) + col;
-    const int64_t stride = isw ? 2 * D * D : 3 * D;
+    const int64_t stride = isw ? 2 * D * D : cols * D;
     const int per = (rows + kGroups - 1) / kGroups;
     const int r0 = g * per, r1 = r0 + per < rows ? r0 + per : rows;
     double acc[4] = {0.0, 0.0, 0.0, 0.0};
@@ -686,20 +915,26 @@ __global__ __launch_bounds__(256) void reduce_kernel(const float* __restrict__ p
         dbr[o] = (float)s;
     } else if (o < 2 * D) {
         dbi[o - D] = (float)s;
-    } else {
+    } else if (o < 3 * D) {
         const double lv = (double)lam[o - 2 * D];
         dlambda[o - 2 * D] = (float)(s / (1.0 + exp(-lv)));
+    } else if (o < 4 * D) {
+        if (dcb) dcb[o - 3 * D] = (float)s;
+    } else {
+        const int64_t j = (o - 4 * D) / D, d = (o - 4 * D) % D;
+        if (j < K) dcw[d * K + j] = (float)s;
     }
 }
 
 constexpr int kMaxGroups = 256;  // workgroups: one per compute unit
+constexpr int kMaxCols = Geo<float, float, true>::kCols;
 
 constexpr size_t pack_bytes(int planes) { return (size_t)2 * D * D * 2 * planes; }
 
 template <typename TX, typename TH, typename TW, bool GATE>
 hipError_t launch(const Params& P, int grid, hipStream_t stream) {
     auto kern = fused_bwd_kernel<TX, TH, TW, GATE>;
-    constexpr int smem = Geo<TX, TW>::kSmem;
+    constexpr int smem = Geo<TX, TW, GATE>::kSmem;
     static const hipError_t attr =
         hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, smem);
     if (attr != hipSuccess) return attr;
@@ -727,7 +962,7 @@ bool fused2_backward_applies(int64_t B, int64_t L, int64_t D, IoType io, const v
 size_t fused2_backward_workspace(int64_t B, int64_t L, int64_t D) {
     if (D != fbw::D || B <= 0 || L <= 0) return 0;
     const size_t grid = (size_t)(B < fbw::kMaxGroups ? B : fbw::kMaxGroups);
-    return 2 * fbw::pack_bytes(2) + grid * (2 * D * D + 3 * D) * sizeof(float);
+    return 2 * fbw::pack_bytes(2) + grid * (2 * D * D + fbw::kMaxCols * D) * sizeof(float);
 }
 
 hipError_t launch_fused2_backward(const Fused2BwdArgs& a, hipStream_t stream) {
@@ -748,7 +983,8 @@ hipError_t launch_fused2_backward(const Fused2BwdArgs& a, hipStream_t stream) {
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const Params P{a.x,  a.h,  a.gy ? a.gy : a.dh, a.gz, a.gdz, a.dx,   a.h0,   a.dhT, a.dh0,
-                   pz,   px,   a.br,               a.bi, a.lambda, part_w, part_c, a.L,  a.B};
+                   pz,   px,   a.br,               a.bi, a.lambda, part_w, part_c, a.L,  a.B,
+                   a.cw, a.cb, a.K};
     if (a.gy)
         e = launch<float, float, float, true>(P, grid, stream);
     else if (f32)
@@ -756,8 +992,10 @@ hipError_t launch_fused2_backward(const Fused2BwdArgs& a, hipStream_t stream) {
     else
         e = launch<bf16, bf16, bf16, false>(P, grid, stream);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(reduce_kernel, dim3(2 * D * D / 64 + 3 * D / 64), dim3(256), 0, stream,
-                       part_w, part_c, grid, a.lambda, a.dwr, a.dwi, a.dbr, a.dbi, a.dlambda);
+    const int cols = a.gy ? kMaxCols : 3;
+    hipLaunchKernelGGL(reduce_kernel, dim3(2 * D * D / 64 + cols * D / 64), dim3(256), 0, stream,
+                       part_w, part_c, grid, a.lambda, a.dwr, a.dwi, a.dbr, a.dbi, a.dlambda, cols,
+                       a.dcw, a.dcb, a.K);
     return hipGetLastError();
 }
 

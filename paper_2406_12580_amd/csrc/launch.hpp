@@ -187,8 +187,10 @@ hipError_t launch_fused_backward(const FusedBwdArgs& a, DlambdaRows* dl, hipStre
 
 // Layer backward in one kernel (fused_bwd.hip): z formed again, the adjoint
 // scan, the gate gradients, dx += dz W and dW = dz^T x, with dz kept on chip.
-// x, h, dh and dx of the I/O type, weights and biases too; gated (fp32 only):
-// dh = gy SiLU(gz) on load and dhz stored to gdz.  ws:
+// x, h, dh and dx of the I/O type, weights and biases too.  Gated (gy set, fp32
+// only) it is the whole backward of the gated layer core: x and dx are hx and
+// dhx, x' = SiLU(conv(hx)) on load (taps cw [D][K], bias cb or null; gradients
+// dcw, and dcb if not null), dh = gy SiLU(gz), dhz stored to gdz.  ws:
 // fused2_backward_workspace bytes, 16-byte aligned.
 struct Fused2BwdArgs {
     const void* x;
@@ -214,6 +216,11 @@ struct Fused2BwdArgs {
     int64_t B, L, D;
     IoType io;
     void* ws;
+    const float* cw = nullptr;
+    const float* cb = nullptr;
+    float* dcw = nullptr;
+    float* dcb = nullptr;
+    int K = 0;
 };
 bool fused2_backward_applies(int64_t B, int64_t L, int64_t D, IoType io, const void* x,
                              const void* h, const void* dx, bool gated);

@@ -289,8 +289,8 @@ def test_full_backward_one_kernel(rb, rows, io, state):
         return
     rng = np.random.Generator(np.random.PCG64(4800 + B + L))
     hz = rng.standard_normal((B, L, D), dtype=np.float32)
-    w = (rng.standard_normal((D, 4)) * 0.5).astype(np.float32)
-    cb = (rng.standard_normal(D) * 0.1).astype(np.float32)
+    w = (rng.standard_normal((D, 1 + L % 4)) * 0.5).astype(np.float32)  # 1 to 4 taps
+    cb = (rng.standard_normal(D) * 0.1).astype(np.float32) if state else None
     args = (dev32(f.x), dev32(hz), dev32(w), dev32(cb), Wr, br, Wi, bi, lam)
     _, h, _ = rb.gated_forward(*args, h0)
     got = rb.gated_backward(*args, h, dev32(f.dh), h0, dhT)
