@@ -604,16 +604,26 @@ int recblr_gated_backward(const void* hx, const void* hz, const float* conv_w,
             fa.gz = hz;
             fa.gdz = bf ? nullptr : dhz;
             fa.h_bf16 = bf;
+            const bool both = project_backward_both_applies(B * L, D, IoType::kF32, dzr, dzi, xp,
+                                                            dxp, at(lws, fl.dw));
+            fa.pack_frag = both;
             if (launch_fused_backward(fa, &dl, strm) != hipSuccess) return RECBLR_ERR_HIP;
             // dx' += dz W (for bf16 I/O with the bf16 weights as given: one
             // operand plane), then dW from fp32 x'.
-            if (launch_project_backward_data(dzr, dzi, W_r, W_i, dxp, B * L, D,
-                                             bf ? IoType::kBf16 : IoType::kF32, pack_dx, strm, bf,
-                                             true) != hipSuccess ||
-                launch_project_backward_weights(dzr, dzi, xp, dW_r, db_r, dW_i, db_i, B * L, D,
-                                                IoType::kF32, at(lws, fl.dw), strm,
-                                                dl) != hipSuccess)
+            if (both) {
+                if (launch_project_backward_both((const float*)dzr, (const float*)dzi, xp, pack_dx,
+                                                 dxp, dW_r, db_r, dW_i, db_i, B * L, D,
+                                                 IoType::kF32, io_of(io), at(lws, fl.dw), dl,
+                                                 strm) != hipSuccess)
+                    return RECBLR_ERR_HIP;
+            } else if (launch_project_backward_data(dzr, dzi, W_r, W_i, dxp, B * L, D,
+                                                    bf ? IoType::kBf16 : IoType::kF32, pack_dx,
+                                                    strm, bf, true) != hipSuccess ||
+                       launch_project_backward_weights(dzr, dzi, xp, dW_r, db_r, dW_i, db_i,
+                                                       B * L, D, IoType::kF32, at(lws, fl.dw),
+                                                       strm, dl) != hipSuccess) {
                 return RECBLR_ERR_HIP;
+            }
             return status_of(launch_conv_backward(hx, dxp, w4, b4, dhx, dconv_w, dconv_b, K, B,
                                                   L, D, io_of(io), IoType::kF32, at(ws, lay.conv),
                                                   strm));
@@ -704,9 +714,19 @@ int recblr_bdlru_backward(const void* x, const void* W_r, const void* b_r, const
     DlambdaRows dl;
     if (fused) {
         // The scan backward recomputes z on the matrix cores (z never reaches HBM).
-        const FusedBwdArgs fa{x,  W_r, W_i, pack, pack_dx, b_r, b_i, lambda, h0, h, dh, dhT, dx, (float*)dzr,
-                              (float*)dzi, dlambda, dh0, B, L, D, io_of(io), at(ws, lay.scan)};
+        FusedBwdArgs fa{x,  W_r, W_i, pack, pack_dx, b_r, b_i, lambda, h0, h, dh, dhT, dx,
+                        (float*)dzr, (float*)dzi, dlambda, dh0, B, L, D, io_of(io),
+                        at(ws, lay.scan)};
+        const bool both = project_backward_both_applies(M, D, io_of(io), dzr, dzi, x, dx,
+                                                        at(ws, lay.dw));
+        fa.pack_frag = both;
         e = launch_fused_backward(fa, &dl, strm);
+        if (both) {
+            if (e != hipSuccess) return RECBLR_ERR_HIP;
+            return status_of(launch_project_backward_both(
+                (const float*)dzr, (const float*)dzi, x, pack_dx, dx, dW_r, db_r, dW_i, db_i, M, D,
+                io_of(io), io_of(io), at(ws, lay.dw), dl, strm));
+        }
     } else {
         e = launch_project_forward(x, W_r, b_r, W_i, b_i, zr, zi, M, D, io_of(io), pack, strm);
         if (e != hipSuccess) return RECBLR_ERR_HIP;

@@ -504,12 +504,15 @@ __global__ __launch_bounds__(256) void pack_kernel(const T* wr, const T* wi, __b
 // launch (each launch costs about 5 us of stream time): the weights ordered by
 // channel group (rows 128 g .. 128 g + 63 are W_r rows of channels 64 g ..
 // 64 g + 63, the next 64 rows the W_i rows of the same channels; D % 64 == 0),
-// for a backward (dx not null) also in the order of the dx product, and the
-// look-back state: n words "not ready", ticket and status 0.
+// for a backward (dx not null) also in the order of the dx product (frag: the
+// fragment order of dxdw_kernel, [32-input block][16-output step][plane][lane][8]:
+// input 32 block + lane % 32, output 16 step + 8 (lane / 32) + e), and the look-back
+// state: n words "not ready", ticket and status 0.
 template <typename T>
 __global__ __launch_bounds__(256) void prepare_kernel(const T* wr, const T* wi, __bf16* groups,
-                                                      __bf16* dx, int64_t D, uint64_t* states,
-                                                      int64_t n, unsigned* ticket) {
+                                                      __bf16* dx, bool frag, int64_t D,
+                                                      uint64_t* states, int64_t n,
+                                                      unsigned* ticket) {
     const int64_t total = 2 * D * D;
     const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     auto put = [&](__bf16* out, float v) {
@@ -521,7 +524,17 @@ __global__ __launch_bounds__(256) void prepare_kernel(const T* wr, const T* wi, 
         const int64_t r = e / D, k = e % D;
         const int64_t ch = (r / 128) * 64 + r % 64;
         put(groups, to_f32(((r / 64) % 2 == 0 ? wr : wi)[ch * D + k]));
-        if (dx) {
+        if (dx && frag) {
+            constexpr int PW = sizeof(T) == 4 ? 2 : 1;
+            const int64_t el = e & 7, lane = (e >> 3) & 63, rest = e >> 9, steps = 2 * D / 16;
+            const int64_t in = 32 * (rest / steps) + (lane & 31);
+            const int64_t out = 16 * (rest % steps) + 8 * (lane >> 5) + el;
+            const float v = out < D ? to_f32(wr[out * D + in]) : to_f32(wi[(out - D) * D + in]);
+            const __bf16 hi = (__bf16)v;
+            __bf16* const dst = dx + (rest * PW * 64 + lane) * 8 + el;
+            dst[0] = hi;
+            if (PW == 2) dst[64 * 8] = (__bf16)(v - (float)hi);
+        } else if (dx) {
             const int64_t in = e / (2 * D), out = e % (2 * D);
             put(dx, out < D ? to_f32(wr[out * D + in]) : to_f32(wi[(out - D) * D + in]));
         }
@@ -1394,7 +1407,7 @@ hipError_t launch_project_backward_data(const void* dzr, const void* dzi, const 
 }
 
 hipError_t launch_prepare_scan(const void* wr, const void* wi, int64_t D, IoType io, void* groups,
-                               void* dx, uint64_t* states, int64_t n, unsigned* ticket,
+                               void* dx, bool frag, uint64_t* states, int64_t n, unsigned* ticket,
                                hipStream_t stream) {
     const int64_t wb = (2 * D * D + 255) / 256;
     int64_t sb = (n + 255) / 256;
@@ -1402,11 +1415,11 @@ hipError_t launch_prepare_scan(const void* wr, const void* wi, int64_t D, IoType
     const dim3 grid((unsigned)(wb > sb ? wb : sb));
     if (io == IoType::kF32)
         hipLaunchKernelGGL(fastmm::prepare_kernel<float>, grid, dim3(256), 0, stream,
-                           (const float*)wr, (const float*)wi, (__bf16*)groups, (__bf16*)dx, D,
+                           (const float*)wr, (const float*)wi, (__bf16*)groups, (__bf16*)dx, frag, D,
                            states, n, ticket);
     else
         hipLaunchKernelGGL(fastmm::prepare_kernel<bf16>, grid, dim3(256), 0, stream,
-                           (const bf16*)wr, (const bf16*)wi, (__bf16*)groups, (__bf16*)dx, D,
+                           (const bf16*)wr, (const bf16*)wi, (__bf16*)groups, (__bf16*)dx, frag, D,
                            states, n, ticket);
     return hipGetLastError();
 }
@@ -1460,7 +1473,19 @@ size_t project_dw_workspace(int64_t M, int64_t D) {
     int64_t splits = 1, rows = 0;
     fastmm::dw_split(M, D, &splits, &rows);
     const size_t fast = (size_t)splits * (size_t)(2 * D) * (size_t)(D + 1) * sizeof(float);
-    return generic > fast ? generic : fast;
+    const size_t both = project_backward_both_workspace(M, D);
+    const size_t most = generic > fast ? generic : fast;
+    return most > both ? most : both;
+}
+
+hipError_t launch_dw_reduce(const float* partial, const float* dbpart, int64_t splits, int64_t D,
+                            float* dwr, float* dbr, float* dwi, float* dbi, const DlambdaRows& dl,
+                            hipStream_t stream) {
+    const int64_t total = 2 * D * D + 2 * D + (dl.rows > 0 ? D : 0);
+    hipLaunchKernelGGL(fastmm::dw_reduce_kernel, dim3((unsigned)((total + 63) / 64)),
+                       dim3(64 * fastmm::kRedGroups), 0, stream, partial, dbpart, splits, D,
+                       2 * D * D, dwr, dbr, dwi, dbi, dl);
+    return hipGetLastError();
 }
 
 hipError_t launch_project_backward_weights(const void* dzr, const void* dzi, const void* x,
@@ -1488,11 +1513,7 @@ hipError_t launch_project_backward_weights(const void* dzr, const void* dzi, con
                                partial, dbpart, M, D, splits, rows_per_split);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
-        const int64_t total = 2 * D * D + 2 * D + (dl.rows > 0 ? D : 0);
-        hipLaunchKernelGGL(fastmm::dw_reduce_kernel, dim3((unsigned)((total + 63) / 64)),
-                           dim3(64 * fastmm::kRedGroups), 0, stream, (const float*)partial,
-                           (const float*)dbpart, splits, D, 2 * D * D, dwr, dbr, dwi, dbi, dl);
-        return hipGetLastError();
+        return launch_dw_reduce(partial, dbpart, splits, D, dwr, dbr, dwi, dbi, dl, stream);
     }
     if (dl.rows > 0) {
         hipLaunchKernelGGL(fastmm::dw_reduce_kernel, dim3((unsigned)((D + 63) / 64)),

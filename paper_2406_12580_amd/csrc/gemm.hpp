@@ -45,13 +45,33 @@ hipError_t launch_project_backward_weights(const void* dzr, const void* dzi, con
                                            hipStream_t stream,
                                            const DlambdaRows& dl = DlambdaRows{});
 
+// The two products above in one pass over dz, where project_backward_both_applies
+// (sizes and types at which it is faster, 16-byte aligned operands): dx += dz W, dW,
+// db and dl's rows.  x and dx of type x_io, weights of type w_io (fp32 x with bf16
+// weights: dx is fp32) packed by launch_prepare_scan with frag; ws:
+// project_dw_workspace(M, D) bytes.
+bool project_backward_both_applies(int64_t M, int64_t D, IoType x_io, const void* dzr,
+                                   const void* dzi, const void* x, const void* dx, const void* ws);
+size_t project_backward_both_workspace(int64_t M, int64_t D);
+hipError_t launch_project_backward_both(const float* dzr, const float* dzi, const void* x,
+                                        const void* pack, void* dx, float* dwr, float* dbr,
+                                        float* dwi, float* dbi, int64_t M, int64_t D, IoType x_io,
+                                        IoType w_io, void* ws, const DlambdaRows& dl,
+                                        hipStream_t stream);
+// The last launch of either: split partials [splits][2 D][D] and [splits][2 D] (and
+// dl's rows) summed in double in a fixed order.
+hipError_t launch_dw_reduce(const float* partial, const float* dbpart, int64_t splits, int64_t D,
+                            float* dwr, float* dbr, float* dwi, float* dbi, const DlambdaRows& dl,
+                            hipStream_t stream);
+
 // What the scans with the projections fused in need first, in one launch:
 // [W_r; W_i] by channel group of 64 (rows 128 g.. : W_r rows of the group's
 // channels, then their W_i rows) into `groups`, with dx not null also in the
-// order of launch_project_backward_data (each project_pack_workspace(D, io)
-// bytes of bf16 planes), and the look-back state (n words, ticket, status).
+// order of launch_project_backward_data or (frag) launch_project_backward_both
+// (each project_pack_workspace(D, io) bytes of bf16 planes), and the look-back state
+// (n words, ticket, status).
 hipError_t launch_prepare_scan(const void* wr, const void* wi, int64_t D, IoType io, void* groups,
-                               void* dx, uint64_t* states, int64_t n, unsigned* ticket,
+                               void* dx, bool frag, uint64_t* states, int64_t n, unsigned* ticket,
                                hipStream_t stream);
 
 // Recurrent step with the gate projections fused in (z stays in registers):

@@ -139,8 +139,9 @@ hipError_t launch_fused2_forward(const void* x, const void* wr, const void* br, 
 // leading positions as identity (embedding padding), L <= 4096.
 // Layer backward's scan with the gate projections recomputed inside
 // (scan_bwd_fused_kernel): x, the weights and room for them packed by channel
-// group and in the order of launch_project_backward_data
-// (project_pack_workspace bytes each), biases (may be null); dx in the I/O
+// group and in the order of launch_project_backward_data or (pack_frag)
+// launch_project_backward_both (project_pack_workspace bytes each), biases (may be
+// null); dx in the I/O
 // type, dz_r and dz_i in fp32, [B][L][D].
 struct FusedBwdArgs {
     const void* x;
@@ -176,6 +177,7 @@ struct FusedBwdArgs {
     // bf16 weights) and the biases in bf16: the gated layer's bf16 backward,
     // which keeps x' and the gradients in fp32.
     bool h_bf16 = false;
+    bool pack_frag = false;
 };
 bool fused_backward_applies(int64_t B, int64_t L, int64_t D, IoType io, const void* x,
                             const void* h, const void* pack);

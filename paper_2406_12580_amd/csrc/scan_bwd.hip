@@ -1073,8 +1073,8 @@ hipError_t launch_fused_backward(const FusedBwdArgs& a, DlambdaRows* dl, hipStre
                       plan.ngroups, plan.nseg, lookback_ws(ws + lay.lb),
                       counters, dlambda_groups(a.D), a.gy, a.gz, a.gdz};
     hipError_t e = launch_prepare_scan(a.wr, a.wi, a.D, a.h_bf16 ? IoType::kBf16 : a.io, a.pack,
-                                       a.pack_dx, P.lb.states, plan.nseg * P.nch, P.lb.ticket,
-                                       stream);
+                                       a.pack_dx, a.pack_frag, P.lb.states, plan.nseg * P.nch,
+                                       P.lb.ticket, stream);
     if (e != hipSuccess) return e;
     const dim3 grid((unsigned)(plan.ngroups * plan.nseg)), block(fusedz::NT);
     const size_t esz = io_bytes(a.io);

@@ -645,7 +645,7 @@ static hipError_t launch_fused_t(const void* x, const void* wr, const void* wi, 
     const FwdPlan plan = plan_fused(B, L, D);
     FwdParams P{x, nullptr, nullptr, lambda, h0, h, hT, L, D, B * D, plan.ngroups, plan.nseg,
                 lookback_ws(ws)};
-    hipError_t e = launch_prepare_scan(wr, wi, D, io, pack, nullptr, P.lb.states,
+    hipError_t e = launch_prepare_scan(wr, wi, D, io, pack, nullptr, false, P.lb.states,
                                        plan.nseg * P.nch, P.lb.ticket, stream);
     if (e != hipSuccess) return e;
     const dim3 grid((unsigned)(plan.ngroups * plan.nseg)), block(fusedz::NT);

@@ -301,6 +301,49 @@ def test_full_backward_one_kernel(rb, rows, io, state):
             assert_close(host(v), want[k], io, k)
 
 
+# Both gradient products of the projections in one pass over dz: 32-row tiles and
+# ranges of at least 256 rows; one part-filled tile, one whole one, a range's edge,
+# ranges of unequal length, and 16384 rows, where fp32 x takes it at D = 192 too.
+@pytest.mark.parametrize("io", ["f32", "bf16"])
+@pytest.mark.parametrize("D", [64, 128, 192, 256])
+@pytest.mark.parametrize("rows", [(3, 7), (1, 32), (2, 128), (3, 257), (128, 129)])
+def test_full_backward_both_products(rb, rows, D, io):
+    B, L = rows
+    if B * L > 16000 and D != 192:
+        pytest.skip("only D = 192 depends on the row count")
+    f = dg.full_inputs(B, L, D, 4900 + B + L + D, io=io, bias=True, grad=True)
+    X, Wr, br, Wi, bi = (dev(a, io) for a in (f.x, f.Wr, f.br, f.Wi, f.bi))
+    lam = dev32(f.lam)
+    h, _ = rb.bdlru_forward(X, Wr, br, Wi, bi, lam)
+    got = rb.bdlru_backward(X, Wr, br, Wi, bi, lam, h, dev(f.dh, io))
+    print(f"both products {rows} {D} {io}: GPU done", flush=True)
+    want = oracle.backward(f.x, f.Wr, f.br, f.Wi, f.bi, f.lam, f.dh)
+    for k in ("dx", "dWr", "dbr", "dWi", "dbi", "dlambda"):
+        assert_close(host(got[k]), want[k], io, k)
+    # the gated layer: fp32 x' with the weights as given
+    rng = np.random.Generator(np.random.PCG64(5000 + B + L + D))
+    hz = rng.standard_normal((B, L, D), dtype=np.float32)
+    if io == "bf16":
+        hz = dg.round_bf16(hz)
+    w = (rng.standard_normal((D, 4)) * 0.5).astype(np.float32)
+    args = (X, dev(hz, io), dev32(w), None, Wr, br, Wi, bi, lam)
+    _, h, _ = rb.gated_forward(*args)
+    got = rb.gated_backward(*args, h, dev(f.dh, io))
+    print(f"both products, gated {rows} {D} {io}: GPU done", flush=True)
+    if io == "f32":
+        want = oracle.gated_backward(f.x, hz, w, None, f.Wr, f.br, f.Wi, f.bi, f.lam, f.dh)
+    else:
+        # The backward reads the h that was stored in bf16.  That rounding (2^-9 of h, in
+        # a dz that is a difference) stays whole in the dW of one row of 32 steps: 1.6e-2
+        # there against the oracle, whose h is exact.  So the oracle's part is taken by
+        # the fp32 entry, checked against it above, on the same numbers and the same h.
+        wide = [None if a is None else a.float() for a in args]
+        want = {k: None if v is None else host(v)
+                for k, v in rb.gated_backward(*wide, h.float(), dev(f.dh)).items()}
+    for k in ("dhx", "dhz", "dconv_w", "dWr", "dbr", "dWi", "dbi", "dlambda"):
+        assert_close(host(got[k]), want[k], io, k)
+
+
 # (B, D): D % 8 == 0 runs the step fused with the projection (z in registers),
 # with a partial channel block for D = 72; D = 130 takes the two-kernel path.
 @pytest.mark.parametrize("io", ["f32", "bf16"])
