@@ -726,6 +726,8 @@ Layout layout(const Dims& d) {
     size_t dwp = (size_t)(slices * NK) * f;
     for (const auto& nk : wshape)
         if (wgrad_workspace(M, nk[0], nk[1]) > dwp) dwp = wgrad_workspace(M, nk[0], nk[1]);
+    if (D == 64 && (size_t)(ffn_backward_ranges(M) * kFfnGrads) * f > dwp)
+        dwp = (size_t)(ffn_backward_ranges(M) * kFfnGrads) * f;
     w.dwp = take(dwp);
     w.wt = take((size_t)NK * f);  // a transposed weight (data gradients)
     // column sums: bias gradients (widths D, 4D, E*D), LayerNorm partials, the
@@ -737,6 +739,8 @@ Layout layout(const Dims& d) {
         const int64_t sp = wgrad_splits(M, nk[0], nk[1]);
         if (colsum_workspace(sp, nk[0] * nk[1]) > cs) cs = colsum_workspace(sp, nk[0] * nk[1]);
     }
+    if (D == 64 && colsum_workspace(ffn_backward_ranges(M), kFfnGrads) > cs)
+        cs = colsum_workspace(ffn_backward_ranges(M), kFfnGrads);
     w.colsum = take(cs);
     const int64_t max_pieces = (M + kPiece - 1) / kPiece + d.V;
     w.emb_lo = take((size_t)d.V * sizeof(int64_t));
@@ -979,6 +983,12 @@ int train_step_t(const Dims& d, const StepOpts& o, const float* params, const in
         CHECK(hipGetLastError() == hipSuccess);
     }
     float* Z = buf(w.Z);
+    // The feed-forward sub-layer in one kernel each way: its four parameters (and
+    // their gradients) lie one after the other, each a whole multiple of 64 floats.
+    auto ffn_fused = [&](int64_t l) {
+        return P(l, kb2) - P(l, kW1) == 2 * F * D + F &&
+               ffn_fused_applies(M, D, F, {ws, P(l, kW1), G(l, kW1)});
+    };
 
     // ---- forward
     CHECK(ln_fwd<NV>(c, E, nullptr, ids, params + off[1], params + off[2], nullptr, Hl(0), mu0,
@@ -997,8 +1007,13 @@ int train_step_t(const Dims& d, const StepOpts& o, const float* params, const in
         CHECK(linear_fwd(c, y, P(l, kWo), P(l, kbo), s1, M, D, ED));
         CHECK(ln_fwd<NV>(c, s1, Hl(l), nullptr, P(l, kLn1g), P(l, kLn1b), s1, H1, stat(l, 0),
                          stat(l, 1), M, V, d.eps, site(1 + 2 * l)));
-        CHECK(linear_fwd(c, H1, P(l, kW1), P(l, kb1), A, M, F, D, Pp));  // Pp = SiLU(A)
-        CHECK(linear_fwd(c, Pp, P(l, kW2), P(l, kb2), s2, M, D, F));
+        if (ffn_fused(l)) {
+            CHECK(launch_ffn_forward(H1, P(l, kW1), P(l, kb1), P(l, kW2), P(l, kb2), A, s2, M,
+                                     stream) == hipSuccess);
+        } else {
+            CHECK(linear_fwd(c, H1, P(l, kW1), P(l, kb1), A, M, F, D, Pp));  // Pp = SiLU(A)
+            CHECK(linear_fwd(c, Pp, P(l, kW2), P(l, kb2), s2, M, D, F));
+        }
         CHECK(ln_fwd<NV>(c, s2, H1, nullptr, P(l, kLn2g), P(l, kLn2b), s2, Hl(l + 1),
                          stat(l, 2), stat(l, 3), M, V, d.eps, site(2 + 2 * l)));
     }
@@ -1033,11 +1048,16 @@ int train_step_t(const Dims& d, const StepOpts& o, const float* params, const in
         CHECK(ln_bwd<NV>(c, Y, s2, nullptr, stat(l, 2), stat(l, 3), P(l, kLn2g), X, G(l, kLn2g),
                          G(l, kLn2b), M, V, site(2 + 2 * l), dropout ? Z : nullptr));
         // PFFN: Q = P W2^T + b2, P = SiLU(A), A = H1 W1^T + b1
-        CHECK(linear_wgrad(c, Pp, dQ, G(l, kW2), G(l, kb2), M, D, F));
-        // dP = (dQ W2) * SiLU'(A)
-        CHECK(linear_dgrad(c, dQ, P(l, kW2), dP, M, D, F, LinearMode::kSiluGrad, A));
-        CHECK(linear_wgrad(c, H1, dP, G(l, kW1), G(l, kb1), M, F, D));
-        CHECK(linear_dgrad(c, dP, P(l, kW1), X, M, F, D, LinearMode::kAccumulate));  // X = dH1
+        if (ffn_fused(l)) {
+            CHECK(launch_ffn_backward(H1, dQ, A, P(l, kW1), P(l, kW2), X, G(l, kW1), M,
+                                      buf(w.dwp), ws + w.colsum, stream) == hipSuccess);
+        } else {
+            CHECK(linear_wgrad(c, Pp, dQ, G(l, kW2), G(l, kb2), M, D, F));
+            // dP = (dQ W2) * SiLU'(A)
+            CHECK(linear_dgrad(c, dQ, P(l, kW2), dP, M, D, F, LinearMode::kSiluGrad, A));
+            CHECK(linear_wgrad(c, H1, dP, G(l, kW1), G(l, kb1), M, F, D));
+            CHECK(linear_dgrad(c, dP, P(l, kW1), X, M, F, D, LinearMode::kAccumulate));  // X = dH1
+        }
         // LN1: X (dH1) -> Y (ds1: the residual part of dH) and dO (ds1 through
         // the dropout, in Z; Y itself without dropout)
         float* dO = dropout ? Z : Y;

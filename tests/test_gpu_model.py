@@ -143,6 +143,30 @@ def test_model_train_step_dropout_padding(rb, case):
     step.close()
 
 
+# The one-kernel sub-layers of D = 64: 32-row tiles and ranges of at least 256 rows; one
+# part-filled tile, one whole one, one row past it, a range's edge.  Without dropout
+# the feed-forward backward reads and accumulates in the same buffer.
+@pytest.mark.parametrize("p", [0.0, 0.2])
+@pytest.mark.parametrize("rows", [(1, 7), (2, 16), (3, 11), (1, 257), (19, 54)])
+def test_model_one_kernel_sublayers(rb, rows, p):
+    import torch
+    dims = dg.ModelDims(B=rows[0], T=rows[1], D=64, E=2, V=50, layers=1, K=4, eps=1e-5)
+    named = dg.model_params(dims, 970 + rows[1])
+    ids, targets = dg.model_batch(dims, 980 + rows[1])
+    rd, P, _ = _device_params(rb, dims, named)
+    step = rb.ModelStep(rd)
+    kw = dict(dropout=p, seed=3, offset=4)
+    loss, grads = step.train_step(P, torch.from_numpy(ids).cuda(),
+                                  torch.from_numpy(targets).cuda(), **kw)
+    torch.cuda.synchronize()
+    print(f"model step {dims} dropout {p}: GPU done", flush=True)
+    flat, _ = _oracle_flat(dims, named)
+    want_loss, want = om.train_step(flat, ids, targets, dims.D, dims.E, dims.V, dims.layers,
+                                    dims.K, dims.eps, **kw)
+    _check_against_oracle(rb, rd, dims, grads.cpu().numpy(), loss.item(), want_loss, want)
+    step.close()
+
+
 def test_adam_update(rb):
     import torch
     rng = np.random.default_rng(5)
