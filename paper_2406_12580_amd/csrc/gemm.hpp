@@ -113,19 +113,34 @@ size_t wgrad_workspace(int64_t M, int64_t N, int64_t K);
 hipError_t launch_wgrad(const float* dy, const float* x, float* dw, float* db, int64_t M,
                         int64_t N, int64_t K, void* ws, void* colsum_ws, hipStream_t stream);
 
-// The model's feed-forward sub-layer Q = SiLU(X W1^T + b1) W2^T + b2 (fp32, D = 64,
-// F = 256, 16-byte aligned operands: ffn_fused_applies), one kernel each way.  The
-// forward stores A = X W1^T + b1 for the backward, which adds to dx and writes
-// [dW1 | db1 | dW2 | db2], contiguous, at grads; part: ffn_backward_ranges(M) rows of
-// kFfnGrads floats, summed by launch_colsum (colsum_ws).
-constexpr int64_t kFfnGrads = 2 * 256 * 64 + 256 + 64;
-bool ffn_fused_applies(int64_t M, int64_t D, int64_t F, std::initializer_list<const void*> ptrs);
-int64_t ffn_backward_ranges(int64_t M);
+// The linear sub-layers of the model (fp32) for D = 64 rows: the feed-forward one,
+// Q = SiLU(X W1^T + b1) W2^T + b2 with 256 hidden units, and the projections around
+// the gated layer, Hx = X Wx^T + bx, Hz = X Wz^T + bz, O = y Wo^T + bo with E = 128
+// (sublayers_fused_applies, 16-byte aligned operands), one kernel each way.  The
+// feed-forward stores A = X W1^T + b1 for its backward.  Backward: adds to dx (for the
+// output projection stores dy) and writes the sub-layer's gradients, contiguous in
+// parameter order, at grads; part: sublayers_fused_workspace(M) bytes, summed by
+// launch_colsum (colsum_ws: sublayers_fused_colsum(M) bytes).
+constexpr int64_t kFfnGrads = 2 * 256 * 64 + 256 + 64;     // dW1, db1, dW2, db2
+constexpr int64_t kProjInGrads = 2 * (128 * 64 + 128);     // dWx, dbx, dWz, dbz
+constexpr int64_t kProjOutGrads = 128 * 64 + 64;           // dWo, dbo
+bool sublayers_fused_applies(int64_t M, int64_t D, std::initializer_list<const void*> ptrs);
+size_t sublayers_fused_workspace(int64_t M);
+size_t sublayers_fused_colsum(int64_t M);
 hipError_t launch_ffn_forward(const float* x, const float* w1, const float* b1, const float* w2,
                               const float* b2, float* a, float* q, int64_t M, hipStream_t stream);
 hipError_t launch_ffn_backward(const float* x, const float* dq, const float* a, const float* w1,
                                const float* w2, float* dx, float* grads, int64_t M, float* part,
                                void* colsum_ws, hipStream_t stream);
+hipError_t launch_proj_in_forward(const float* x, const float* wx, const float* bx,
+                                  const float* wz, const float* bz, float* hx, float* hz,
+                                  int64_t M, hipStream_t stream);
+hipError_t launch_proj_in_backward(const float* x, const float* dhx, const float* dhz,
+                                   const float* wx, const float* wz, float* dx, float* grads,
+                                   int64_t M, float* part, void* colsum_ws, hipStream_t stream);
+hipError_t launch_proj_out_backward(const float* y, const float* dout, const float* w, float* dy,
+                                    float* grads, int64_t M, float* part, void* colsum_ws,
+                                    hipStream_t stream);
 
 int64_t project_dw_splits(int64_t M, int64_t D);
 size_t project_dw_workspace(int64_t M, int64_t D);

@@ -726,8 +726,7 @@ Layout layout(const Dims& d) {
     size_t dwp = (size_t)(slices * NK) * f;
     for (const auto& nk : wshape)
         if (wgrad_workspace(M, nk[0], nk[1]) > dwp) dwp = wgrad_workspace(M, nk[0], nk[1]);
-    if (D == 64 && (size_t)(ffn_backward_ranges(M) * kFfnGrads) * f > dwp)
-        dwp = (size_t)(ffn_backward_ranges(M) * kFfnGrads) * f;
+    if (D == 64 && sublayers_fused_workspace(M) > dwp) dwp = sublayers_fused_workspace(M);
     w.dwp = take(dwp);
     w.wt = take((size_t)NK * f);  // a transposed weight (data gradients)
     // column sums: bias gradients (widths D, 4D, E*D), LayerNorm partials, the
@@ -739,8 +738,7 @@ Layout layout(const Dims& d) {
         const int64_t sp = wgrad_splits(M, nk[0], nk[1]);
         if (colsum_workspace(sp, nk[0] * nk[1]) > cs) cs = colsum_workspace(sp, nk[0] * nk[1]);
     }
-    if (D == 64 && colsum_workspace(ffn_backward_ranges(M), kFfnGrads) > cs)
-        cs = colsum_workspace(ffn_backward_ranges(M), kFfnGrads);
+    if (D == 64 && sublayers_fused_colsum(M) > cs) cs = sublayers_fused_colsum(M);
     w.colsum = take(cs);
     const int64_t max_pieces = (M + kPiece - 1) / kPiece + d.V;
     w.emb_lo = take((size_t)d.V * sizeof(int64_t));
@@ -983,12 +981,11 @@ int train_step_t(const Dims& d, const StepOpts& o, const float* params, const in
         CHECK(hipGetLastError() == hipSuccess);
     }
     float* Z = buf(w.Z);
-    // The feed-forward sub-layer in one kernel each way: its four parameters (and
-    // their gradients) lie one after the other, each a whole multiple of 64 floats.
-    auto ffn_fused = [&](int64_t l) {
-        return P(l, kb2) - P(l, kW1) == 2 * F * D + F &&
-               ffn_fused_applies(M, D, F, {ws, P(l, kW1), G(l, kW1)});
-    };
+    // The linear sub-layers in one kernel each way, where their rows are 64 wide.  Each
+    // one's parameters (and gradients) lie one after the other without padding: their
+    // sizes are multiples of 64 floats.
+    const bool ffn_fused = sublayers_fused_applies(M, D, {ws, params, grads});
+    const bool proj_fused = ffn_fused && ED == 128;
 
     // ---- forward
     CHECK(ln_fwd<NV>(c, E, nullptr, ids, params + off[1], params + off[2], nullptr, Hl(0), mu0,
@@ -997,8 +994,13 @@ int train_step_t(const Dims& d, const StepOpts& o, const float* params, const in
         float *Hx = per(w.Hx, l, ED), *Hz = per(w.Hz, l, ED), *hb = per(w.hb, l, ED),
               *y = per(w.y, l, ED), *s1 = per(w.s1, l, D), *H1 = per(w.H1, l, D),
               *A = per(w.A, l, F), *Pp = per(w.P, l, F), *s2 = per(w.s2, l, D);
-        CHECK(linear_fwd(c, Hl(l), P(l, kWx), P(l, kbx), Hx, M, ED, D));
-        CHECK(linear_fwd(c, Hl(l), P(l, kWz), P(l, kbz), Hz, M, ED, D));
+        if (proj_fused) {
+            CHECK(launch_proj_in_forward(Hl(l), P(l, kWx), P(l, kbx), P(l, kWz), P(l, kbz), Hx, Hz,
+                                         M, stream) == hipSuccess);
+        } else {
+            CHECK(linear_fwd(c, Hl(l), P(l, kWx), P(l, kbx), Hx, M, ED, D));
+            CHECK(linear_fwd(c, Hl(l), P(l, kWz), P(l, kbz), Hz, M, ED, D));
+        }
         CHECK_ST(recblr_gated_forward(Hx, Hz, P(l, kConvW), P(l, kConvB), d.K, P(l, kWr),
                                       P(l, kbr), P(l, kWi), P(l, kbi), P(l, kLam), nullptr, y, hb,
                                       nullptr, B, T, ED, RECBLR_F32, ws + w.gated, w.gated_bytes,
@@ -1007,7 +1009,7 @@ int train_step_t(const Dims& d, const StepOpts& o, const float* params, const in
         CHECK(linear_fwd(c, y, P(l, kWo), P(l, kbo), s1, M, D, ED));
         CHECK(ln_fwd<NV>(c, s1, Hl(l), nullptr, P(l, kLn1g), P(l, kLn1b), s1, H1, stat(l, 0),
                          stat(l, 1), M, V, d.eps, site(1 + 2 * l)));
-        if (ffn_fused(l)) {
+        if (ffn_fused) {
             CHECK(launch_ffn_forward(H1, P(l, kW1), P(l, kb1), P(l, kW2), P(l, kb2), A, s2, M,
                                      stream) == hipSuccess);
         } else {
@@ -1048,7 +1050,7 @@ int train_step_t(const Dims& d, const StepOpts& o, const float* params, const in
         CHECK(ln_bwd<NV>(c, Y, s2, nullptr, stat(l, 2), stat(l, 3), P(l, kLn2g), X, G(l, kLn2g),
                          G(l, kLn2b), M, V, site(2 + 2 * l), dropout ? Z : nullptr));
         // PFFN: Q = P W2^T + b2, P = SiLU(A), A = H1 W1^T + b1
-        if (ffn_fused(l)) {
+        if (ffn_fused) {
             CHECK(launch_ffn_backward(H1, dQ, A, P(l, kW1), P(l, kW2), X, G(l, kW1), M,
                                       buf(w.dwp), ws + w.colsum, stream) == hipSuccess);
         } else {
@@ -1064,8 +1066,13 @@ int train_step_t(const Dims& d, const StepOpts& o, const float* params, const in
         CHECK(ln_bwd<NV>(c, X, s1, nullptr, stat(l, 0), stat(l, 1), P(l, kLn1g), Y, G(l, kLn1g),
                          G(l, kLn1b), M, V, site(1 + 2 * l), dropout ? Z : nullptr));
         // O = y Wo^T + bo
-        CHECK(linear_wgrad(c, y, dO, G(l, kWo), G(l, kbo), M, D, ED));
-        CHECK(linear_dgrad(c, dO, P(l, kWo), dY, M, D, ED, LinearMode::kStore));
+        if (proj_fused) {
+            CHECK(launch_proj_out_backward(y, dO, P(l, kWo), dY, G(l, kWo), M, buf(w.dwp),
+                                           ws + w.colsum, stream) == hipSuccess);
+        } else {
+            CHECK(linear_wgrad(c, y, dO, G(l, kWo), G(l, kbo), M, D, ED));
+            CHECK(linear_dgrad(c, dO, P(l, kWo), dY, M, D, ED, LinearMode::kStore));
+        }
         CHECK_ST(recblr_gated_backward(Hx, Hz, P(l, kConvW), P(l, kConvB), d.K, P(l, kWr),
                                        P(l, kbr), P(l, kWi), P(l, kbi), P(l, kLam), nullptr, hb,
                                        dY, nullptr, dHx, dHz, G(l, kConvW), G(l, kConvB),
@@ -1073,10 +1080,15 @@ int train_step_t(const Dims& d, const StepOpts& o, const float* params, const in
                                        nullptr, B, T, ED, RECBLR_F32, ws + w.gated, w.gated_bytes,
                                        stream));
         // Hx = H Wx^T + bx, Hz = H Wz^T + bz; Y becomes dH of this layer's input.
-        CHECK(linear_wgrad(c, Hl(l), dHx, G(l, kWx), G(l, kbx), M, ED, D));
-        CHECK(linear_wgrad(c, Hl(l), dHz, G(l, kWz), G(l, kbz), M, ED, D));
-        CHECK(linear_dgrad(c, dHx, P(l, kWx), Y, M, ED, D, LinearMode::kAccumulate));
-        CHECK(linear_dgrad(c, dHz, P(l, kWz), Y, M, ED, D, LinearMode::kAccumulate));
+        if (proj_fused) {
+            CHECK(launch_proj_in_backward(Hl(l), dHx, dHz, P(l, kWx), P(l, kWz), Y, G(l, kWx), M,
+                                          buf(w.dwp), ws + w.colsum, stream) == hipSuccess);
+        } else {
+            CHECK(linear_wgrad(c, Hl(l), dHx, G(l, kWx), G(l, kbx), M, ED, D));
+            CHECK(linear_wgrad(c, Hl(l), dHz, G(l, kWz), G(l, kbz), M, ED, D));
+            CHECK(linear_dgrad(c, dHx, P(l, kWx), Y, M, ED, D, LinearMode::kAccumulate));
+            CHECK(linear_dgrad(c, dHz, P(l, kWz), Y, M, ED, D, LinearMode::kAccumulate));
+        }
     }
     // embedding LayerNorm, then the input side of dE: rows summed per item
     CHECK(ln_bwd<NV>(c, Y, E, ids, mu0, rs0, params + off[1], X, grads + off[1], grads + off[2], M,
