@@ -167,6 +167,34 @@ def test_model_one_kernel_sublayers(rb, rows, p):
     step.close()
 
 
+# The embedding gradient's grouping of positions by item: a count per item and run of 256
+# positions up to 16384 items, a sort beyond; runs with one position, items in several
+# runs and pieces, tables around the 1024 threads and 64 lanes that walk them.
+@pytest.mark.parametrize("shape", [(1, 2, 2), (1, 256, 63), (1, 257, 64), (4, 200, 65),
+                                   (3, 100, 1024), (2, 129, 1025), (70, 100, 7),
+                                   (2, 40, 16384), (2, 40, 16385)])
+def test_model_embedding_grouping(rb, shape):
+    import torch
+    B, T, V = shape
+    dims = dg.ModelDims(B=B, T=T, D=64, E=1, V=V, layers=1, K=2, eps=1e-5)
+    named = dg.model_params(dims, 990 + V)
+    rng = np.random.default_rng(V)
+    ids = rng.integers(0, V, (B, T)).astype(np.int32)
+    ids[0, 0], ids[-1, -1] = V - 1, 0
+    targets = rng.integers(0, V, B).astype(np.int32)
+    rd, P, _ = _device_params(rb, dims, named)
+    step = rb.ModelStep(rd)
+    loss, grads = step.train_step(P, torch.from_numpy(ids).cuda(),
+                                  torch.from_numpy(targets).cuda())
+    torch.cuda.synchronize()
+    print(f"model step {dims}: GPU done", flush=True)
+    flat, _ = _oracle_flat(dims, named)
+    want_loss, want = om.train_step(flat, ids, targets, dims.D, dims.E, dims.V, dims.layers,
+                                    dims.K, dims.eps)
+    _check_against_oracle(rb, rd, dims, grads.cpu().numpy(), loss.item(), want_loss, want)
+    step.close()
+
+
 def test_adam_update(rb):
     import torch
     rng = np.random.default_rng(5)
