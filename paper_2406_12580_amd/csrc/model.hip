@@ -219,8 +219,8 @@ __global__ __launch_bounds__(kThreads) void ln_fwd_kernel(
 // workgroup handles rows [blk * kLnBwdRows, + kLnBwdRows) in wave accesses of
 // RPA rows (wave w takes accesses w, w + 4, ...); each lane sums dy xh and dy
 // of its four features over its rows in order, then the RPA row slots of a
-// wave and the four waves are added in a fixed order into pg[blk], pb[blk]
-// (summed over workgroups later).
+// wave and the four waves are added in a fixed order into row blk of the
+// [workgroups][2 D] partials pg (pb: its second half; ln_params_kernel sums them).
 template <int NV, bool EMB, bool DROP>
 __global__ __launch_bounds__(kThreads) void ln_bwd_kernel(
     const float* __restrict__ dy, const float* __restrict__ s, const int* __restrict__ ids,
@@ -363,9 +363,43 @@ __global__ __launch_bounds__(kThreads) void ln_bwd_kernel(
             tg = float4{tg.x + ug.x, tg.y + ug.y, tg.z + ug.z, tg.w + ug.w};
             tb = float4{tb.x + ub.x, tb.y + ub.y, tb.z + ub.z, tb.w + ub.w};
         }
-        st4(pg + blockIdx.x * D + c, tg);
-        st4(pb + blockIdx.x * D + c, tb);
+        st4(pg + (int64_t)blockIdx.x * 2 * D + c, tg);
+        st4(pb + (int64_t)blockIdx.x * 2 * D + c, tb);
     }
+}
+
+// gamma and beta gradients of every LayerNorm in one launch at the step's end: part is
+// [site][rows][2 D], site 0 the embedding's, 1 + 2 l and 2 + 2 l layer l's, whose
+// gradients (gamma, then beta) start at ln1 + l stride and ln2 + l stride.  A workgroup
+// sums 64 columns of a site in double: 16 waves take a range of rows each, 16 loads in
+// flight, and the range sums are added in order.  Each of two sums a site and two stages
+// a sum was a launch of about 5 us (20 in a step of two layers: 110 us; this one 9 us).
+constexpr int kLnWaves = 16;
+__global__ __launch_bounds__(kLnWaves * kWave) void ln_params_kernel(
+    const float* __restrict__ part, int64_t rows, int cols, float* __restrict__ grads,
+    int64_t emb, int64_t ln1, int64_t ln2, int64_t stride) {
+    __shared__ double sh[kLnWaves][kWave];
+    constexpr int N = 16;
+    const int lane = threadIdx.x & (kWave - 1), q = wave_id(), site = blockIdx.y;
+    const int c = blockIdx.x * kWave + lane;
+    const float* const p = part + (int64_t)site * rows * cols + c;
+    const int64_t per = (rows + kLnWaves - 1) / kLnWaves;
+    const int64_t r1 = (q + 1) * per < rows ? (q + 1) * per : rows;
+    double acc = 0.0;
+    for (int64_t r = q * per; r < r1; r += N) {
+        float v[N];
+#pragma unroll
+        for (int k = 0; k < N; ++k) v[k] = p[(r + k < r1 ? r + k : r1 - 1) * cols];
+#pragma unroll
+        for (int k = 0; k < N; ++k)
+            if (r + k < r1) acc += (double)v[k];
+    }
+    sh[q][lane] = acc;
+    __syncthreads();
+    if (q != 0) return;
+    for (int k = 1; k < kLnWaves; ++k) acc += sh[k][lane];
+    const int64_t l = (site - 1) / 2;
+    grads[(site == 0 ? emb : (site & 1 ? ln1 : ln2) + l * stride) + c] = (float)acc;
 }
 
 // ------------------------------------------------------------------ elementwise
@@ -853,7 +887,7 @@ Layout layout(const Dims& d) {
     w.dHx = take((size_t)(M * ED) * f);
     w.dHz = take((size_t)(M * ED) * f);
     const int64_t lnblk = (M + kLnBwdRows - 1) / kLnBwdRows;
-    w.lnp = take((size_t)(2 * lnblk * D) * f);
+    w.lnp = take((size_t)((2 * L + 1) * 2 * lnblk * D) * f);  // of every LayerNorm
     // weight gradients: one partial per chunk of kDwChunk rows, summed after
     const int64_t NK = 4 * D * D > ED * D ? 4 * D * D : ED * D;
     const int64_t slices = M / kDwChunk + 1;
@@ -866,10 +900,8 @@ Layout layout(const Dims& d) {
     if (D == 64 && sublayers_fused_workspace(M) > dwp) dwp = sublayers_fused_workspace(M);
     w.dwp = take(dwp);
     w.wt = take((size_t)NK * f);  // a transposed weight (data gradients)
-    // column sums: bias gradients (widths D, 4D, E*D), LayerNorm partials, the
-    // weight-gradient slices or splits
+    // column sums: bias gradients (widths D, 4D, E*D), the weight-gradient slices or splits
     size_t cs = colsum_workspace(M, F > ED ? F : ED);
-    if (colsum_workspace(lnblk, D) > cs) cs = colsum_workspace(lnblk, D);
     if (colsum_workspace(slices, NK) > cs) cs = colsum_workspace(slices, NK);
     for (const auto& nk : wshape) {
         const int64_t sp = wgrad_splits(M, nk[0], nk[1]);
@@ -1042,16 +1074,16 @@ bool ln_fwd(Ctx& c, const float* a, const float* r, const int* ids, const float*
     return hipGetLastError() == hipSuccess;
 }
 
-// LayerNorm backward; gamma / beta gradients into dg, db; dxm (non-embedding,
+// LayerNorm backward; gamma / beta partials of site k (ln_params_kernel); dxm (non-embedding,
 // may be null) the gradient of the dropped-out sub-layer output.
 template <int NV>
 bool ln_bwd(Ctx& c, const float* dy, const float* s, const int* ids, const float* mu,
-            const float* rs, const float* g, float* dx, float* dg, float* db, int64_t M,
-            int64_t V, Drop dr, float* dxm = nullptr) {
+            const float* rs, const float* g, float* dx, int64_t k, int64_t M, int64_t V, Drop dr,
+            float* dxm = nullptr) {
     constexpr int D = 64 * NV;
     const int64_t nblk = (M + kLnBwdRows - 1) / kLnBwdRows;
-    float* pg = (float*)(c.ws + c.w.lnp);
-    float* pb = pg + nblk * D;
+    float* pg = (float*)(c.ws + c.w.lnp) + k * nblk * 2 * D;
+    float* pb = pg + D;
     // The kernel reads the keep bits and writes dxm together (non-EMB).
     const bool drop = dr.keep != nullptr;
     if (!ids && drop != (dxm != nullptr)) return false;
@@ -1066,9 +1098,7 @@ bool ln_bwd(Ctx& c, const float* dy, const float* s, const int* ids, const float
         drop ? run(T_{}, T_{}) : run(T_{}, F_{});
     else
         drop ? run(F_{}, T_{}) : run(F_{}, F_{});
-    if (hipGetLastError() != hipSuccess) return false;
-    return launch_colsum(pg, nblk, D, dg, c.ws + c.w.colsum, c.stream) == hipSuccess &&
-           launch_colsum(pb, nblk, D, db, c.ws + c.w.colsum, c.stream) == hipSuccess;
+    return hipGetLastError() == hipSuccess;
 }
 
 template <int NV>
@@ -1190,8 +1220,8 @@ int train_step_t(const Dims& d, const StepOpts& o, const float* params, const in
         // LN2: Y (dH2) -> X (ds2: the residual part of dH1) and dQ (ds2 through
         // the dropout, in Z; X itself without dropout)
         float* dQ = dropout ? Z : X;
-        CHECK(ln_bwd<NV>(c, Y, s2, nullptr, stat(l, 2), stat(l, 3), P(l, kLn2g), X, G(l, kLn2g),
-                         G(l, kLn2b), M, V, site(2 + 2 * l), dropout ? Z : nullptr));
+        CHECK(ln_bwd<NV>(c, Y, s2, nullptr, stat(l, 2), stat(l, 3), P(l, kLn2g), X, 2 + 2 * l,
+                         M, V, site(2 + 2 * l), dropout ? Z : nullptr));
         // PFFN: Q = P W2^T + b2, P = SiLU(A), A = H1 W1^T + b1
         if (ffn_fused) {
             CHECK(launch_ffn_backward(H1, dQ, A, P(l, kW1), P(l, kW2), X, G(l, kW1), M,
@@ -1206,8 +1236,8 @@ int train_step_t(const Dims& d, const StepOpts& o, const float* params, const in
         // LN1: X (dH1) -> Y (ds1: the residual part of dH) and dO (ds1 through
         // the dropout, in Z; Y itself without dropout)
         float* dO = dropout ? Z : Y;
-        CHECK(ln_bwd<NV>(c, X, s1, nullptr, stat(l, 0), stat(l, 1), P(l, kLn1g), Y, G(l, kLn1g),
-                         G(l, kLn1b), M, V, site(1 + 2 * l), dropout ? Z : nullptr));
+        CHECK(ln_bwd<NV>(c, X, s1, nullptr, stat(l, 0), stat(l, 1), P(l, kLn1g), Y, 1 + 2 * l,
+                         M, V, site(1 + 2 * l), dropout ? Z : nullptr));
         // O = y Wo^T + bo
         if (proj_fused) {
             CHECK(launch_proj_out_backward(y, dO, P(l, kWo), dY, G(l, kWo), M, buf(w.dwp),
@@ -1234,8 +1264,16 @@ int train_step_t(const Dims& d, const StepOpts& o, const float* params, const in
         }
     }
     // embedding LayerNorm, then the input side of dE: rows summed per item
-    CHECK(ln_bwd<NV>(c, Y, E, ids, mu0, rs0, params + off[1], X, grads + off[1], grads + off[2], M,
-                     V, site(0, o.pad_id)));
+    CHECK(ln_bwd<NV>(c, Y, E, ids, mu0, rs0, params + off[1], X, 0, M, V,
+                     site(0, o.pad_id)));
+    // gamma and beta lie one after the other (sizes are multiples of 64 floats), the layers
+    // one stride apart.
+    const int64_t lstride = d.layers > 1 ? off[3 + kLayerTensors] - off[3] : 0;
+    hipLaunchKernelGGL(ln_params_kernel, dim3((unsigned)(2 * D / kWave), 2 * d.layers + 1),
+                       dim3(kLnWaves * kWave), 0, stream, buf(w.lnp),
+                       (M + kLnBwdRows - 1) / kLnBwdRows, (int)(2 * D), grads, off[1],
+                       off[3 + kLn1g], off[3 + kLn2g], lstride);
+    CHECK(hipGetLastError() == hipSuccess);
     int* pos_s = (int*)(ws + w.pos_s);
     int64_t* lo = (int64_t*)(ws + w.emb_lo);
     int64_t* hi = (int64_t*)(ws + w.emb_hi);
