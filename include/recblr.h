@@ -304,9 +304,11 @@ int recblr_gated_backward(const void* hx, const void* hz, const float* conv_w,
  * id (recblr_model_step_opts) enter as the zero vector: left padding with
  * zeros (section 3.3).  The linear layers of the behaviour-modelling layers run on
  * this library's matrix-core kernels (fp32 products for the forward and the
- * data gradients; bias, SiLU and its derivative fused in); the prediction
- * layer's products are rocBLAS fp32 GEMMs; all other steps run in this
- * library's kernels.
+ * data gradients; bias, SiLU and its derivative fused in), as does the
+ * prediction (fp32 products), and all other steps run in its kernels too;
+ * operands that the matrix-core kernels do not take go to rocBLAS.  Behind its
+ * scan the last layer runs on the last step's rows only, forward and backward:
+ * the others reach neither the loss nor any gradient.
  *
  * Parameters are one flat float buffer, each tensor starting at a multiple of
  * 64 floats (recblr_model_param_offsets), weights [out][in], in this order:
@@ -363,7 +365,7 @@ typedef struct {
     uint64_t offset; /* Philox key, word 1 */
 } recblr_model_step_opts;
 
-/* rocBLAS handle for the model step's prediction-layer GEMMs: created and
+/* rocBLAS handle for the model step's library GEMMs (see above): created and
  * destroyed by the caller (creation allocates rocBLAS' own state; the step
  * itself allocates nothing).  A handle serves one stream at a time. */
 int recblr_blas_create(void** handle);

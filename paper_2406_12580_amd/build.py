@@ -19,8 +19,8 @@ BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(HERE, "librecblr.so")
 SOURCES = ["capi.cpp", "scan_fwd.hip", "scan_bwd.hip", "step.hip", "gemm.hip", "ablation.hip",
            "gated.hip", "model.hip", "noalloc.hip", "fused_fwd.hip", "fused_bwd.hip",
-           "proj_bwd.hip", "ffn.hip"]
-# The prediction layer of the full-model step uses rocBLAS GEMMs.
+           "proj_bwd.hip", "ffn.hip", "head.hip"]
+# Linear layers that the matrix-core tiles do not take go to rocBLAS.
 LIBS = ["-L/opt/rocm/lib", "-lrocblas"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"

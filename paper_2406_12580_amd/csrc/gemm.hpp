@@ -145,4 +145,14 @@ hipError_t launch_proj_out_backward(const float* y, const float* dout, const flo
 int64_t project_dw_splits(int64_t M, int64_t D);
 size_t project_dw_workspace(int64_t M, int64_t D);
 
+// The prediction head in fp32 (head.hip), D a multiple of 64, at most 512:
+// logits = h E^T, dE = dlogits^T h and dh = dlogits E, all stored (not added).  h and
+// dh [B][D], E and dE [V][D], logits and dlogits [B][V]; ws: B V floats of scratch.
+hipError_t launch_head_logits(const float* h, const float* E, float* logits, int64_t B, int64_t V,
+                              int64_t D, hipStream_t stream);
+hipError_t launch_head_dE(const float* dlogits, const float* h, float* dE, int64_t B, int64_t V,
+                          int64_t D, hipStream_t stream);
+hipError_t launch_head_dh(const float* dlogits, const float* E, float* dh, int64_t B, int64_t V,
+                          int64_t D, float* ws, hipStream_t stream);
+
 }  // namespace recblr

@@ -8,13 +8,14 @@
 // The linear layers of the behaviour-modelling layers run on the matrix-core
 // kernels of gemm.hip (fp32 MFMAs for forward products and data gradients,
 // with the bias, SiLU and SiLU' in their epilogues; bf16-split tiles for the
-// weight gradients); the prediction layer's products are rocBLAS fp32 GEMMs;
+// weight gradients; at D = 64 whole sub-layers in the kernels of ffn.hip), the
+// prediction layer's products on those of head.hip;
 // everything else runs in the kernels of this library: the gated recurrent layer core through
 // recblr_gated_forward / recblr_gated_backward (conv, BD-LRU scan with its
 // gate projections, output gate), and here the embedding gather, the
 // LayerNorms, bias broadcasts, SiLU, the cross entropy, the sums over rows
 // for bias and LayerNorm gradients (fixed order, double), the embedding
-// gradient (positions sorted by item, then summed per item in position
+// gradient (positions grouped by item, then summed per item in position
 // order), the dropout masks (one bit per element from a counter-based
 // generator, applied inside the LayerNorm kernels) and Adam.
 #include <hip/hip_runtime.h>
@@ -81,14 +82,24 @@ __device__ __forceinline__ void philox4x64_10(uint64_t (&c)[4], uint64_t k0, uin
 // word w of site s is element e = 32 w + b of that site, taken from 32-bit
 // word e mod 8 (low half of each 64-bit output first) of Philox4x64-10 at
 // counter (e / 8, s, 0, 0) under key (seed, offset); the element is kept when
-// that word is at least thr = floor(p 2^32).  One thread per mask word.
+// that word is at least thr = floor(p 2^32).  One thread per mask word.  From site
+// `compact` on only the last step's rows are drawn, one after the other: `last` words
+// a site, row r of rw words being the site's row (r + 1) T - 1.
 __global__ __launch_bounds__(kThreads) void dropout_mask_kernel(uint32_t* __restrict__ mask,
                                                                 int64_t words, int64_t total,
+                                                                int64_t compact, int64_t last,
+                                                                int64_t rw, int64_t T,
                                                                 uint32_t thr, uint64_t seed,
                                                                 uint64_t offset) {
     const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
     if (i >= total) return;
-    const int64_t site = i / words, w = i - site * words;
+    int64_t site = i / words, w = i - site * words;
+    if (i >= compact * words) {
+        const int64_t j = i - compact * words;
+        site = compact + j / last;
+        w = j % last;
+        w = ((w / rw + 1) * T - 1) * rw + w % rw;
+    }
     uint32_t bits = 0;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
@@ -369,20 +380,21 @@ __global__ __launch_bounds__(kThreads) void ln_bwd_kernel(
 }
 
 // gamma and beta gradients of every LayerNorm in one launch at the step's end: part is
-// [site][rows][2 D], site 0 the embedding's, 1 + 2 l and 2 + 2 l layer l's, whose
+// [site][rows][2 D] (from site `compact` on only rows_c of the rows are there), site 0 the embedding's, 1 + 2 l and 2 + 2 l layer l's, whose
 // gradients (gamma, then beta) start at ln1 + l stride and ln2 + l stride.  A workgroup
 // sums 64 columns of a site in double: 16 waves take a range of rows each, 16 loads in
 // flight, and the range sums are added in order.  Each of two sums a site and two stages
 // a sum was a launch of about 5 us (20 in a step of two layers: 110 us; this one 9 us).
 constexpr int kLnWaves = 16;
 __global__ __launch_bounds__(kLnWaves * kWave) void ln_params_kernel(
-    const float* __restrict__ part, int64_t rows, int cols, float* __restrict__ grads,
-    int64_t emb, int64_t ln1, int64_t ln2, int64_t stride) {
+    const float* __restrict__ part, int64_t rows, int compact, int64_t rows_c, int cols,
+    float* __restrict__ grads, int64_t emb, int64_t ln1, int64_t ln2, int64_t stride) {
     __shared__ double sh[kLnWaves][kWave];
     constexpr int N = 16;
     const int lane = threadIdx.x & (kWave - 1), q = wave_id(), site = blockIdx.y;
     const int c = blockIdx.x * kWave + lane;
     const float* const p = part + (int64_t)site * rows * cols + c;
+    if (site >= compact) rows = rows_c;
     const int64_t per = (rows + kLnWaves - 1) / kLnWaves;
     const int64_t r1 = (q + 1) * per < rows ? (q + 1) * per : rows;
     double acc = 0.0;
@@ -400,6 +412,55 @@ __global__ __launch_bounds__(kLnWaves * kWave) void ln_params_kernel(
     for (int k = 1; k < kLnWaves; ++k) acc += sh[k][lane];
     const int64_t l = (site - 1) / 2;
     grads[(site == 0 ? emb : (site & 1 ? ln1 : ln2) + l * stride) + c] = (float)acc;
+}
+
+// ------------------------------------------------------------------ the last step's rows
+// The prediction reads the last layer's output at the last step only, and behind that
+// layer's scan every sub-layer works on rows by themselves.  So the output projection,
+// the feed-forward sub-layer, their LayerNorms and dropouts run on those B rows, forward
+// and backward: the other B (T - 1) rows reach neither the loss nor, their gradient being
+// zero, any gradient.  MovieLens-1M step (B = 2048, T = 200, D = 64, two layers):
+// 4524 -> 3666 us; the spread of the two gradients back over all steps takes 46 us of it.
+//
+// dst[b] = src[(b + 1) T - 1], rows of w floats (w % 4 == 0), of two tensors at once.
+__global__ __launch_bounds__(kThreads) void last_rows_kernel(const float* __restrict__ s0,
+                                                             float* __restrict__ d0, int64_t w0,
+                                                             const float* __restrict__ s1,
+                                                             float* __restrict__ d1, int64_t w1,
+                                                             int64_t B, int64_t T) {
+    const int64_t q0 = w0 / 4, q = q0 + w1 / 4;
+    const int64_t e = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+    if (e >= B * q) return;
+    const int64_t b = e / q, c = e - b * q, row = (b + 1) * T - 1;
+    if (c < q0)
+        st4(d0 + b * w0 + 4 * c, ld4(s0 + row * w0 + 4 * c));
+    else
+        st4(d1 + b * w1 + 4 * (c - q0), ld4(s1 + row * w1 + 4 * (c - q0)));
+}
+// The other way: all T rows of every b, zero before the last one.  A workgroup writes
+// kSpreadRows consecutive rows; bound by the stores.
+constexpr int64_t kSpreadRows = 16;
+__global__ __launch_bounds__(kThreads) void spread_rows_kernel(const float* __restrict__ s0,
+                                                               float* __restrict__ d0, int w0,
+                                                               const float* __restrict__ s1,
+                                                               float* __restrict__ d1, int w1,
+                                                               int64_t B, int64_t T) {
+    const int q0 = w0 / 4, q = q0 + w1 / 4;
+    const int64_t r0 = (int64_t)blockIdx.x * kSpreadRows;
+    const int n = (int)(B * T - r0 < kSpreadRows ? B * T - r0 : kSpreadRows);
+    for (int e = threadIdx.x; e < n * q; e += kThreads) {
+        const int r = e / q, c = e - r * q;
+        const int64_t row = r0 + r, b = row / T;
+        const bool last = row - b * T == T - 1;
+        float4 v{0.0f, 0.0f, 0.0f, 0.0f};
+        if (c < q0) {
+            if (last) v = ld4(s0 + b * w0 + 4 * c);
+            st4(d0 + row * w0 + 4 * c, v);
+        } else {
+            if (last) v = ld4(s1 + b * w1 + 4 * (c - q0));
+            st4(d1 + row * w1 + 4 * (c - q0), v);
+        }
+    }
 }
 
 // ------------------------------------------------------------------ elementwise
@@ -637,14 +698,16 @@ __global__ __launch_bounds__(1024) void emb_ranges_kernel(const int* __restrict_
                                                           int64_t* __restrict__ poff) {
     __shared__ uint64_t sums[1024 / kWave];
     const int lane = threadIdx.x & (kWave - 1), w = wave_id();
+    constexpr int PER = (int)(kCountKeys / 1024);
     const int per = (V + 1023) / 1024;
     const int v0 = threadIdx.x * per, v1 = v0 + per < V ? v0 + per : V;
-    auto word = [&](int v) {
-        const int64_t n = total[v];
-        return (uint64_t)n << 32 | (uint64_t)((n + kPiece - 1) / kPiece);
-    };
-    uint64_t own = 0;
-    for (int v = v0; v < v1; ++v) own += word(v);
+    uint64_t word[PER], own = 0;  // of this thread's items
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const int n = k < per && v0 + k < V ? total[v0 + k] : 0;
+        word[k] = (uint64_t)n << 32 | (uint64_t)((n + kPiece - 1) / kPiece);
+        own += word[k];
+    }
     uint64_t at = own;  // inclusive over the wave
 #pragma unroll
     for (int o = 1; o < kWave; o <<= 1) {
@@ -655,10 +718,13 @@ __global__ __launch_bounds__(1024) void emb_ranges_kernel(const int* __restrict_
     __syncthreads();
     at -= own;
     for (int p = 0; p < w; ++p) at += sums[p];
-    for (int v = v0; v < v1; ++v) {
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const int v = v0 + k;
+        if (v >= v1) break;
         lo[v] = (int64_t)(at >> 32);
         poff[v] = (int64_t)(at & 0xffffffffu);
-        at += word(v);
+        at += word[k];
         hi[v] = (int64_t)(at >> 32);
         if (v == V - 1) poff[V] = (int64_t)(at & 0xffffffffu);
     }
@@ -842,7 +908,8 @@ int64_t param_offsets(const Dims& d, int64_t* off) {
 struct Layout {
     size_t H, Hx, Hz, hb, y, s1, H1, A, P, s2, stats, emb_stats, logits, dlogits, lossb;
     size_t X, Y, Z, dP, dY, dHx, dHz, lnp, dwp, wt, colsum, emb_lo, emb_hi, emb_np, emb_poff,
-        emb_part, mask;
+        emb_part, mask, yL, HL;
+    int64_t lnp_site;  // floats of a LayerNorm's partials
     size_t ids_s, pos, pos_s, sort_tmp, emb_cnt, gated, total;
     size_t sort_bytes, gated_bytes;
 };
@@ -887,6 +954,9 @@ Layout layout(const Dims& d) {
     w.dHx = take((size_t)(M * ED) * f);
     w.dHz = take((size_t)(M * ED) * f);
     const int64_t lnblk = (M + kLnBwdRows - 1) / kLnBwdRows;
+    w.lnp_site = 2 * lnblk * D;
+    w.yL = take((size_t)(d.B * ED) * f);  // the last layer's y and input at the last step
+    w.HL = take((size_t)(d.B * D) * f);
     w.lnp = take((size_t)((2 * L + 1) * 2 * lnblk * D) * f);  // of every LayerNorm
     // weight gradients: one partial per chunk of kDwChunk rows, summed after
     const int64_t NK = 4 * D * D > ED * D ? 4 * D * D : ED * D;
@@ -895,19 +965,23 @@ Layout layout(const Dims& d) {
     // the bias gradient's partials after them)
     const int64_t wshape[4][2] = {{D, F}, {F, D}, {D, ED}, {ED, D}};
     size_t dwp = (size_t)(slices * NK) * f;
-    for (const auto& nk : wshape)
-        if (wgrad_workspace(M, nk[0], nk[1]) > dwp) dwp = wgrad_workspace(M, nk[0], nk[1]);
-    if (D == 64 && sublayers_fused_workspace(M) > dwp) dwp = sublayers_fused_workspace(M);
+    for (const int64_t m : {M, d.B}) {  // the last layer's sub-layers run on B rows
+        for (const auto& nk : wshape)
+            if (wgrad_workspace(m, nk[0], nk[1]) > dwp) dwp = wgrad_workspace(m, nk[0], nk[1]);
+        if (D == 64 && sublayers_fused_workspace(m) > dwp) dwp = sublayers_fused_workspace(m);
+    }
     w.dwp = take(dwp);
     w.wt = take((size_t)NK * f);  // a transposed weight (data gradients)
     // column sums: bias gradients (widths D, 4D, E*D), the weight-gradient slices or splits
     size_t cs = colsum_workspace(M, F > ED ? F : ED);
     if (colsum_workspace(slices, NK) > cs) cs = colsum_workspace(slices, NK);
-    for (const auto& nk : wshape) {
-        const int64_t sp = wgrad_splits(M, nk[0], nk[1]);
-        if (colsum_workspace(sp, nk[0] * nk[1]) > cs) cs = colsum_workspace(sp, nk[0] * nk[1]);
+    for (const int64_t m : {M, d.B}) {
+        for (const auto& nk : wshape) {
+            const int64_t sp = wgrad_splits(m, nk[0], nk[1]);
+            if (colsum_workspace(sp, nk[0] * nk[1]) > cs) cs = colsum_workspace(sp, nk[0] * nk[1]);
+        }
+        if (D == 64 && sublayers_fused_colsum(m) > cs) cs = sublayers_fused_colsum(m);
     }
-    if (D == 64 && sublayers_fused_colsum(M) > cs) cs = sublayers_fused_colsum(M);
     w.colsum = take(cs);
     const int64_t max_pieces = (M + kPiece - 1) / kPiece + d.V;
     w.emb_lo = take((size_t)d.V * sizeof(int64_t));
@@ -1082,7 +1156,7 @@ bool ln_bwd(Ctx& c, const float* dy, const float* s, const int* ids, const float
             float* dxm = nullptr) {
     constexpr int D = 64 * NV;
     const int64_t nblk = (M + kLnBwdRows - 1) / kLnBwdRows;
-    float* pg = (float*)(c.ws + c.w.lnp) + k * nblk * 2 * D;
+    float* pg = (float*)(c.ws + c.w.lnp) + k * c.w.lnp_site;
     float* pb = pg + D;
     // The kernel reads the keep bits and writes dxm together (non-EMB).
     const bool drop = dr.keep != nullptr;
@@ -1136,21 +1210,24 @@ int train_step_t(const Dims& d, const StepOpts& o, const float* params, const in
     // ---- dropout masks: every site's keep bits, drawn once for the step
     const bool dropout = o.dropout > 0.0f;
     const int64_t mwords = mask_words(d);
+    const int64_t full_sites = mask_sites(d) - 2, lwords = B * (D / 32);
     uint32_t* mask = (uint32_t*)(ws + w.mask);
     auto site = [&](int64_t k, int pad = -1) {
         Drop dr;
         dr.pad = pad;
         if (dropout) {
-            dr.keep = mask + k * mwords;
+            dr.keep = k < full_sites ? mask + k * mwords
+                                     : mask + full_sites * mwords + (k - full_sites) * lwords;
             dr.scale = 1.0f / (1.0f - o.dropout);
         }
         return dr;
     };
     if (dropout) {
-        const int64_t total = mask_sites(d) * mwords;
+        const int64_t total = full_sites * mwords + (mask_sites(d) - full_sites) * lwords;
         const uint32_t thr = (uint32_t)floor((double)o.dropout * 4294967296.0);
         hipLaunchKernelGGL(dropout_mask_kernel, dim3(blocks_for(total)), dim3(kThreads), 0,
-                           stream, mask, mwords, total, thr, o.seed, o.offset);
+                           stream, mask, mwords, total, full_sites, lwords, D / 32, T, thr, o.seed,
+                           o.offset);
         CHECK(hipGetLastError() == hipSuccess);
     }
     float* Z = buf(w.Z);
@@ -1179,24 +1256,35 @@ int train_step_t(const Dims& d, const StepOpts& o, const float* params, const in
                                       nullptr, B, T, ED, RECBLR_F32, ws + w.gated, w.gated_bytes,
                                       stream));
         // O = y Wo^T + bo goes to s1, then s1 += H and H1 = LN(s1).
-        CHECK(linear_fwd(c, y, P(l, kWo), P(l, kbo), s1, M, D, ED));
-        CHECK(ln_fwd<NV>(c, s1, Hl(l), nullptr, P(l, kLn1g), P(l, kLn1b), s1, H1, stat(l, 0),
-                         stat(l, 1), M, V, d.eps, site(1 + 2 * l)));
+        const bool top = l == d.layers - 1;  // from here on at the last step only
+        const int64_t R = top ? B : M;
+        const float *yr = y, *Hr = Hl(l);
+        if (top) {
+            hipLaunchKernelGGL(last_rows_kernel, dim3(blocks_for(B * (ED + D) / 4)),
+                               dim3(kThreads), 0, stream, y, buf(w.yL), ED, Hl(l), buf(w.HL), D, B,
+                               T);
+            CHECK(hipGetLastError() == hipSuccess);
+            yr = buf(w.yL);
+            Hr = buf(w.HL);
+        }
+        CHECK(linear_fwd(c, yr, P(l, kWo), P(l, kbo), s1, R, D, ED));
+        CHECK(ln_fwd<NV>(c, s1, Hr, nullptr, P(l, kLn1g), P(l, kLn1b), s1, H1, stat(l, 0),
+                         stat(l, 1), R, V, d.eps, site(1 + 2 * l)));
         if (ffn_fused) {
-            CHECK(launch_ffn_forward(H1, P(l, kW1), P(l, kb1), P(l, kW2), P(l, kb2), A, s2, M,
+            CHECK(launch_ffn_forward(H1, P(l, kW1), P(l, kb1), P(l, kW2), P(l, kb2), A, s2, R,
                                      stream) == hipSuccess);
         } else {
-            CHECK(linear_fwd(c, H1, P(l, kW1), P(l, kb1), A, M, F, D, Pp));  // Pp = SiLU(A)
-            CHECK(linear_fwd(c, Pp, P(l, kW2), P(l, kb2), s2, M, D, F));
+            CHECK(linear_fwd(c, H1, P(l, kW1), P(l, kb1), A, R, F, D, Pp));  // Pp = SiLU(A)
+            CHECK(linear_fwd(c, Pp, P(l, kW2), P(l, kb2), s2, R, D, F));
         }
         CHECK(ln_fwd<NV>(c, s2, H1, nullptr, P(l, kLn2g), P(l, kLn2b), s2, Hl(l + 1),
-                         stat(l, 2), stat(l, 3), M, V, d.eps, site(2 + 2 * l)));
+                         stat(l, 2), stat(l, 3), R, V, d.eps, site(2 + 2 * l)));
     }
     // prediction: logits = h_T E^T with h_T the last step of every row
-    const float* hT = Hl(d.layers) + (T - 1) * D;
+    const float* hT = Hl(d.layers);
     float* logits = buf(w.logits);
     float* dlogits = buf(w.dlogits);
-    CHECK(gemm_xwT(c, hT, T * D, E, logits, V, B, V, D, 0.0f));
+    CHECK(launch_head_logits(hT, E, logits, B, V, D, stream) == hipSuccess);
     hipLaunchKernelGGL(ce_kernel, dim3((unsigned)B), dim3(kThreads), 0, stream, logits, targets, B,
                        V, dlogits, buf(w.lossb));
     CHECK(hipGetLastError() == hipSuccess);
@@ -1209,42 +1297,51 @@ int train_step_t(const Dims& d, const StepOpts& o, const float* params, const in
           *dHz = buf(w.dHz);
     float* dE = grads + off[0];
     // dE = dlogits^T h_T (the prediction's use of E); the input side adds on later.
-    CHECK(gemm_dyTx(c, hT, T * D, dlogits, V, dE, B, V, D));
-    // dH of the last layer's output: zero except the last step, dlogits E.
-    CHECK(launch_fill(Y, 0.0f, M * D, stream) == hipSuccess);
-    CHECK(gemm_dyW(c, dlogits, V, E, Y + (T - 1) * D, T * D, B, V, D, 0.0f));
+    CHECK(launch_head_dE(dlogits, hT, dE, B, V, D, stream) == hipSuccess);
+    // dH of the last layer's output at the last step
+    CHECK(launch_head_dh(dlogits, E, Y, B, V, D, logits, stream) == hipSuccess);
     for (int64_t l = d.layers - 1; l >= 0; --l) {
         float *Hx = per(w.Hx, l, ED), *Hz = per(w.Hz, l, ED), *hb = per(w.hb, l, ED),
               *y = per(w.y, l, ED), *s1 = per(w.s1, l, D), *H1 = per(w.H1, l, D),
               *A = per(w.A, l, F), *Pp = per(w.P, l, F), *s2 = per(w.s2, l, D);
         // LN2: Y (dH2) -> X (ds2: the residual part of dH1) and dQ (ds2 through
         // the dropout, in Z; X itself without dropout)
+        const bool top = l == d.layers - 1;
+        const int64_t R = top ? B : M;
         float* dQ = dropout ? Z : X;
         CHECK(ln_bwd<NV>(c, Y, s2, nullptr, stat(l, 2), stat(l, 3), P(l, kLn2g), X, 2 + 2 * l,
-                         M, V, site(2 + 2 * l), dropout ? Z : nullptr));
+                         R, V, site(2 + 2 * l), dropout ? Z : nullptr));
         // PFFN: Q = P W2^T + b2, P = SiLU(A), A = H1 W1^T + b1
         if (ffn_fused) {
-            CHECK(launch_ffn_backward(H1, dQ, A, P(l, kW1), P(l, kW2), X, G(l, kW1), M,
+            CHECK(launch_ffn_backward(H1, dQ, A, P(l, kW1), P(l, kW2), X, G(l, kW1), R,
                                       buf(w.dwp), ws + w.colsum, stream) == hipSuccess);
         } else {
-            CHECK(linear_wgrad(c, Pp, dQ, G(l, kW2), G(l, kb2), M, D, F));
+            CHECK(linear_wgrad(c, Pp, dQ, G(l, kW2), G(l, kb2), R, D, F));
             // dP = (dQ W2) * SiLU'(A)
-            CHECK(linear_dgrad(c, dQ, P(l, kW2), dP, M, D, F, LinearMode::kSiluGrad, A));
-            CHECK(linear_wgrad(c, H1, dP, G(l, kW1), G(l, kb1), M, F, D));
-            CHECK(linear_dgrad(c, dP, P(l, kW1), X, M, F, D, LinearMode::kAccumulate));  // X = dH1
+            CHECK(linear_dgrad(c, dQ, P(l, kW2), dP, R, D, F, LinearMode::kSiluGrad, A));
+            CHECK(linear_wgrad(c, H1, dP, G(l, kW1), G(l, kb1), R, F, D));
+            CHECK(linear_dgrad(c, dP, P(l, kW1), X, R, F, D, LinearMode::kAccumulate));  // X = dH1
         }
         // LN1: X (dH1) -> Y (ds1: the residual part of dH) and dO (ds1 through
         // the dropout, in Z; Y itself without dropout)
-        float* dO = dropout ? Z : Y;
-        CHECK(ln_bwd<NV>(c, X, s1, nullptr, stat(l, 0), stat(l, 1), P(l, kLn1g), Y, 1 + 2 * l,
-                         M, V, site(1 + 2 * l), dropout ? Z : nullptr));
+        // (top: B rows of each in dHx and dHz, which nothing else holds yet)
+        float *ds1 = top ? dHx : Y, *dYr = top ? dHz : dY;
+        const float* yr = top ? buf(w.yL) : y;
+        float* dO = dropout ? Z : ds1;
+        CHECK(ln_bwd<NV>(c, X, s1, nullptr, stat(l, 0), stat(l, 1), P(l, kLn1g), ds1, 1 + 2 * l,
+                         R, V, site(1 + 2 * l), dropout ? Z : nullptr));
         // O = y Wo^T + bo
         if (proj_fused) {
-            CHECK(launch_proj_out_backward(y, dO, P(l, kWo), dY, G(l, kWo), M, buf(w.dwp),
+            CHECK(launch_proj_out_backward(yr, dO, P(l, kWo), dYr, G(l, kWo), R, buf(w.dwp),
                                            ws + w.colsum, stream) == hipSuccess);
         } else {
-            CHECK(linear_wgrad(c, y, dO, G(l, kWo), G(l, kbo), M, D, ED));
-            CHECK(linear_dgrad(c, dO, P(l, kWo), dY, M, D, ED, LinearMode::kStore));
+            CHECK(linear_wgrad(c, yr, dO, G(l, kWo), G(l, kbo), R, D, ED));
+            CHECK(linear_dgrad(c, dO, P(l, kWo), dYr, R, D, ED, LinearMode::kStore));
+        }
+        if (top) {
+            hipLaunchKernelGGL(spread_rows_kernel, dim3(blocks_for(M, kSpreadRows)),
+                               dim3(kThreads), 0, stream, dYr, dY, (int)ED, ds1, Y, (int)D, B, T);
+            CHECK(hipGetLastError() == hipSuccess);
         }
         CHECK_ST(recblr_gated_backward(Hx, Hz, P(l, kConvW), P(l, kConvB), d.K, P(l, kWr),
                                        P(l, kbr), P(l, kWi), P(l, kbi), P(l, kLam), nullptr, hb,
@@ -1271,7 +1368,8 @@ int train_step_t(const Dims& d, const StepOpts& o, const float* params, const in
     const int64_t lstride = d.layers > 1 ? off[3 + kLayerTensors] - off[3] : 0;
     hipLaunchKernelGGL(ln_params_kernel, dim3((unsigned)(2 * D / kWave), 2 * d.layers + 1),
                        dim3(kLnWaves * kWave), 0, stream, buf(w.lnp),
-                       (M + kLnBwdRows - 1) / kLnBwdRows, (int)(2 * D), grads, off[1],
+                       (M + kLnBwdRows - 1) / kLnBwdRows, (int)full_sites,
+                       (B + kLnBwdRows - 1) / kLnBwdRows, (int)(2 * D), grads, off[1],
                        off[3 + kLn1g], off[3 + kLn2g], lstride);
     CHECK(hipGetLastError() == hipSuccess);
     int* pos_s = (int*)(ws + w.pos_s);

@@ -195,6 +195,34 @@ def test_model_embedding_grouping(rb, shape):
     step.close()
 
 
+# The prediction head's kernels: tiles of 32 batch rows and 32 or 64 items or features, the
+# contractions over B and V in 8 ranges of whole groups of 16 (fewer rows than a group, one
+# past a group, a tile, all ranges), items around a workgroup's 512, and from 1024 items
+# the contraction over V split over workgroups.
+@pytest.mark.parametrize("shape", [(1, 2, 64), (15, 33, 128), (33, 31, 64), (129, 511, 64),
+                                   (31, 513, 256), (300, 145, 64),
+                                   (2, 1024, 64), (33, 1600, 128)])
+def test_model_head(rb, shape):
+    import torch
+    B, V, D = shape
+    dims = dg.ModelDims(B=B, T=2, D=D, E=1, V=V, layers=1, K=2, eps=1e-5)
+    named = dg.model_params(dims, 880 + V)
+    rng = np.random.default_rng(V)
+    ids = rng.integers(0, V, (B, 2)).astype(np.int32)
+    targets = rng.integers(0, V, B).astype(np.int32)
+    rd, P, _ = _device_params(rb, dims, named)
+    step = rb.ModelStep(rd)
+    loss, grads = step.train_step(P, torch.from_numpy(ids).cuda(),
+                                  torch.from_numpy(targets).cuda())
+    torch.cuda.synchronize()
+    print(f"model step {dims}: GPU done", flush=True)
+    flat, _ = _oracle_flat(dims, named)
+    want_loss, want = om.train_step(flat, ids, targets, dims.D, dims.E, dims.V, dims.layers,
+                                    dims.K, dims.eps)
+    _check_against_oracle(rb, rd, dims, grads.cpu().numpy(), loss.item(), want_loss, want)
+    step.close()
+
+
 def test_adam_update(rb):
     import torch
     rng = np.random.default_rng(5)
