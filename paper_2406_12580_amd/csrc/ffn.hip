@@ -797,10 +797,13 @@ hipError_t allow_lds(K kern, int bytes) {
     return hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
 }
 
-// `most` workgroups (one or two per compute unit); at least 256 rows a range (each
-// leaves a partial).
+// `most` workgroups (one or two per compute unit), a tile or more each: every range
+// leaves a partial of its weight gradients to sum, but few rows in few ranges leave the
+// chip idle (model step of 2000 rows, two layers: 437 us with at least 256 rows a range,
+// 376 with 64, 371 with 32; 20000 rows, one layer: 411, 375 and 370 us).
+constexpr int64_t kMinRows = TR;
 void split(int64_t M, int64_t most, int64_t* ranges, int64_t* rows) {
-    int64_t n = (M + 255) / 256;
+    int64_t n = (M + kMinRows - 1) / kMinRows;
     n = n < most ? n : most;
     *rows = ((M + n - 1) / n + TR - 1) / TR * TR;
     *ranges = (M + *rows - 1) / *rows;
