@@ -20,6 +20,15 @@ constexpr int kWave = 64;
 __device__ __forceinline__ int wave_id() {
     return __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
 }
+
+// Hand-over through LDS between lanes of one wave.  The hardware executes a wave's
+// LDS operations in order, but the compiler sees one lane's addresses only and may move
+// a lane's read of another lane's slot across its own writes (and the other way round).
+// No instruction: the comment marks the place in the assembly.
+__device__ __forceinline__ void wave_fence() {
+    asm volatile("; wave_fence" ::: "memory");
+    __builtin_amdgcn_wave_barrier();
+}
 constexpr float kLog2e = 1.4426950408889634f;
 
 // ------------------------------------------------------------------ I/O types

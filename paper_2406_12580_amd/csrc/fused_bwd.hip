@@ -349,6 +349,7 @@ __global__ __launch_bounds__(NT, 2) void fused_bwd_kernel(Params P) {
             for (int m = 0; m < 2; ++m)
 #pragma unroll
                 for (int i = 0; i < 8; ++i) *(float*)(hb + (32 * m + i) * (D * 4)) = hx[m][i];
+            wave_fence();  // the window's first steps are other lanes'
 #pragma unroll
             for (int k = 0; k < 3; ++k) before[k] = hxb[k];
 #pragma unroll
@@ -646,6 +647,7 @@ __global__ __launch_bounds__(NT, 2) void fused_bwd_kernel(Params P) {
                                fmaf(wt[0], dc[i], fmaf(wt[1], dc[i + 1],
                                                        fmaf(wt[2], dc[i + 2], wt[3] * dc[i + 3]))));
             }
+            wave_fence();  // stage() overwrites the steps that other lanes read here
             dcb += sb;
 #pragma unroll
             for (int j = 0; j < 4; ++j) dcw[j] += sw[j];

@@ -1,0 +1,50 @@
+"""Hand-overs through LDS between the lanes of one wave, in the compiled kernels.
+
+The lanes of a wave run in step, so no barrier instruction is needed, but nothing in one
+lane's own addresses tells the compiler that its read depends on another lane's write.
+wave_fence() (device_common.hpp) does, and leaves a comment in the assembly; each
+hand-over has to show it between the LDS accesses that it orders.
+"""
+import os
+import subprocess
+
+import pytest
+
+from paper_2406_12580_amd import build as hipbuild
+
+
+def _assembly(tmp_path, source):
+    out = os.path.join(tmp_path, "k.s")
+    cmd = [hipbuild.HIPCC, "-x", "hip", *hipbuild.FLAGS, "--cuda-device-only", "-S", source,
+           "-o", out]
+    res = subprocess.run(cmd, capture_output=True, text=True, timeout=300)
+    assert res.returncode == 0, res.stderr
+    with open(out) as f:
+        return f.read().splitlines()
+
+
+def _lds_runs(lines, kernel):
+    """The kernel's LDS accesses (R, W), fences (F) and barriers (B) in listing order, runs
+    of one kind as one letter."""
+    first = next(i for i, l in enumerate(lines) if l.startswith("_Z") and kernel in l)
+    ops = ""
+    for l in lines[first:]:
+        l = l.strip()
+        if l.startswith(".Lfunc_end"):
+            break
+        op = ("R" if l.startswith("ds_read") else "W" if l.startswith("ds_write") else
+              "B" if l.startswith("s_barrier") else "F" if l.startswith("; wave_fence") else "")
+        if op and not ops.endswith(op):
+            ops += op
+    return ops
+
+
+# The gated layer's one-kernel backward: the staged hx of the steps before a lane's own
+# (twice: before the loop and in it), and those steps in the conv's backward (whole tile,
+# last tile) before the next tile's are written over them.
+def test_gated_backward_conv_window(tmp_path):
+    source = os.path.join(hipbuild.CSRC, "fused_bwd.hip")
+    ops = _lds_runs(_assembly(tmp_path, source), "fused_bwd_kernelIfffLb1E")
+    print(ops)
+    assert ops.startswith("WFR"), ops
+    assert ops.count("WFR") == 2 and ops.count("RF") == 2, ops
