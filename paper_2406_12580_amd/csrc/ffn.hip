@@ -431,6 +431,7 @@ __global__ __launch_bounds__(NT, 2) void ffn_bwd_kernel(BwdParams P) {
         const __amdgpu_buffer_rsrc_t drs = rsrc(P.dx + m * D, (uint32_t)(n * D * 4));
         const u4v dd = __builtin_amdgcn_raw_buffer_load_b128(drs, dx_off(ln, w), 0, 0);
         __builtin_amdgcn_sched_barrier(0);
+        wave_fence();  // get_block reads what other lanes put
         // ---- this wave's part of dX^T
         f16v o[2];
 #pragma unroll
@@ -642,6 +643,7 @@ __global__ __launch_bounds__(NT, 2) void proj_in_bwd_kernel(InBwdParams P) {
         const __amdgpu_buffer_rsrc_t drs = rsrc(P.dx + m * D, (uint32_t)(n * D * 4));
         const u4v dd = __builtin_amdgcn_raw_buffer_load_b128(drs, dx_off(ln, w), 0, 0);
         __builtin_amdgcn_sched_barrier(0);
+        wave_fence();  // get_block reads what other lanes put
         f16v o[2];
 #pragma unroll
         for (int db = 0; db < 2; ++db)

@@ -48,3 +48,17 @@ def test_gated_backward_conv_window(tmp_path):
     print(ops)
     assert ops.startswith("WFR"), ops
     assert ops.count("WFR") == 2 and ops.count("RF") == 2, ops
+
+
+# The D = 64 sub-layers' backward: a wave's block of gradients transposed through its own
+# LDS (written by unit, read by row).
+@pytest.mark.parametrize("kernel", ["ffn_bwd_kernel", "proj_in_bwd_kernel"])
+def test_sublayer_transposed_block(tmp_path, kernel):
+    source = os.path.join(hipbuild.CSRC, "ffn.hip")
+    ops = _lds_runs(_assembly(tmp_path, source), kernel)
+    print(ops)
+    loop = ops[ops.index("B"):]  # after the first rows are staged
+    assert loop.count("F") == 1, ops
+    before, after = loop.split("F")
+    assert "W" in before and before.count("B") == 1, ops  # the block, then the fence
+    assert after.startswith("RB"), ops
