@@ -119,7 +119,8 @@ __device__ __forceinline__ void tile_z(const T* x, const __bf16* pack, const TW*
     // Bias, then the strip to the lane-per-channel layout, one gate at a time
     // through a wave-private LDS strip of 64 columns: column c (16 consecutive
     // steps) becomes lane c's z_r, then its z_i.  A wave's LDS operations
-    // execute in order, so the second gate may reuse the strip.
+    // execute in order, so the second gate may reuse the strip; wave_fence()
+    // keeps the compiler to that order.
     float* zs = (float*)smem + w * 64 * ZP;
     const ElemReader<TW> rbr(br, D), rbi(bi, D);
     const int64_t d = cg * kWave + (lane & 15);
@@ -131,6 +132,7 @@ __device__ __forceinline__ void tile_z(const T* x, const __bf16* pack, const TW*
             const float bias = gate == 0 ? rbr(d + 16 * j) : rbi(d + 16 * j);
             *(f4*)&zs[col * ZP + 4 * (lane >> 4)] = acc[4 * gate + j] + f4{bias, bias, bias, bias};
         }
+        wave_fence();
         float* dst = gate == 0 ? zr : zi;
 #pragma unroll
         for (int q = 0; q < C / 4; ++q) {
@@ -138,6 +140,7 @@ __device__ __forceinline__ void tile_z(const T* x, const __bf16* pack, const TW*
 #pragma unroll
             for (int e = 0; e < 4; ++e) dst[4 * q + e] = v[e];
         }
+        if (gate == 0) wave_fence();
     }
 }
 

@@ -62,3 +62,26 @@ def test_sublayer_transposed_block(tmp_path, kernel):
     before, after = loop.split("F")
     assert "W" in before and before.count("B") == 1, ops  # the block, then the fence
     assert after.startswith("RB"), ops
+
+
+# The tile product of the fused scans: each gate's strip written by accumulator rows and
+# read by channel, the second gate's over the first one's.
+def test_tile_product_strip(tmp_path):
+    source = os.path.join(tmp_path, "probe.hip")
+    with open(source, "w") as f:
+        f.write("""#include "fused_z.hpp"
+using namespace recblr;
+__global__ __launch_bounds__(fusedz::NT) void probe_kernel(
+    const float* x, const __bf16* pack, const float* br, const float* bi, int64_t L, int64_t D,
+    float* out) {
+    __shared__ __attribute__((aligned(16))) char smem[fusedz::Tile<float>::kSmem];
+    const int tid = threadIdx.x, w = wave_id(), lane = tid & 63;
+    float zr[fusedz::C], zi[fusedz::C];
+    fusedz::tile_z<float>(x, pack, br, bi, L, D, 0, blockIdx.x, 0, smem, tid, w, lane, zr, zi);
+    for (int c = 0; c < fusedz::C; ++c) out[(blockIdx.x * fusedz::NT + tid) * 32 + c] = zr[c];
+    for (int c = 0; c < fusedz::C; ++c) out[(blockIdx.x * fusedz::NT + tid) * 32 + 16 + c] = zi[c];
+}
+""")
+    ops = _lds_runs(_assembly(tmp_path, source), "probe_kernel")
+    print(ops)
+    assert ops.endswith("WFRFWFR"), ops
