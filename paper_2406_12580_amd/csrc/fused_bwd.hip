@@ -29,8 +29,9 @@
 // channel's whole dx' from the LDS tile back through the conv, walking the tiles
 // from the end as the adjoint does, so that dc of the three later steps is at hand.
 // Products of two fp32 operands are the 3-term bf16 split of fastmm (hi*hi +
-// hi*lo + lo*hi); bf16 operands are one exact plane.  dW, db and dLambda leave
-// as one fp32 partial per workgroup, summed in double in a fixed order by
+// hi*lo + lo*hi); bf16 operands are one exact plane.  The sums over steps and rows (db, dLambda,
+// the conv's gradients) are fp32 within a tile and double across tiles; they and dW
+// leave as one fp32 partial per workgroup, summed in double in a fixed order by
 // reduce_kernel.  Nothing depends on the order in which workgroups run.
 //
 // What it replaces and costs (256 x 2048 x 128 fp32): the fused scan, which
@@ -135,6 +136,17 @@ __device__ __forceinline__ float half_partner(float v, bool upper) {
     return __uint_as_float(upper ? r[0] : r[1]);
 }
 
+// Four values summed over the four 16-lane rows of the wave: row r gets value r's sum.
+__device__ __forceinline__ float row_sums(float a, float b, float c, float d) {
+    swap16(a, b);  // a: rows 0 and 2 of a, of b; b: rows 1 and 3 of a, of b
+    swap16(c, d);
+    a += b;
+    c += d;
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(c), false,
+                                                    false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const void* p, uint32_t bytes) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, (int)bytes,
                                              0x00020000);
@@ -221,12 +233,14 @@ __global__ __launch_bounds__(NT, 2) void fused_bwd_kernel(Params P) {
         for (int c = 0; c < 2; ++c)
 #pragma unroll
             for (int v = 0; v < 16; ++v) dw[a][c][v] = 0.0f;
-    float nbr, nbi, dbr = 0.0f, dbi = 0.0f, dl = 0.0f, carry = 0.0f;
+    float nbr, nbi, carry = 0.0f;
     ChannelConst cc;
-    // GATE: the lane's channel's taps and bias, their gradients, dc of the three
-    // steps after the tile, hx of the three before it
-    float wt[GATE ? 4 : 1], cbv = 0.0f, dcw[GATE ? 4 : 1], dcb = 0.0f, later[GATE ? 3 : 1],
-        before[GATE ? 3 : 1];
+    // Totals over the workgroup's tiles of the lane's channel, lane row rho: db_r, db_i,
+    // dLoss/dq r or (GATE) the conv bias's gradient, and (GATE) the gradient of tap rho.
+    double total = 0.0, total_w = 0.0;
+    // GATE: the lane's channel's taps and bias, the last tile's part of the bias's gradient,
+    // dc of the three steps after the tile, hx of the three before it
+    float wt[GATE ? 4 : 1], cbv = 0.0f, dcb = 0.0f, later[GATE ? 3 : 1], before[GATE ? 3 : 1];
     {
         const int ch = 16 * w + (lane & 15);
         nbr = P.br ? -load((const TW*)P.br + ch) * kLog2e : 0.0f;
@@ -235,10 +249,7 @@ __global__ __launch_bounds__(NT, 2) void fused_bwd_kernel(Params P) {
         if constexpr (GATE) {
             cbv = P.cb ? P.cb[ch] : 0.0f;
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                wt[j] = j < P.K ? P.cw[ch * P.K + j] : 0.0f;
-                dcw[j] = 0.0f;
-            }
+            for (int j = 0; j < 4; ++j) wt[j] = j < P.K ? P.cw[ch * P.K + j] : 0.0f;
         }
     }
 
@@ -583,9 +594,7 @@ __global__ __launch_bounds__(NT, 2) void fused_bwd_kernel(Params P) {
                 *(u4v*)(dst + G::kDzPlane) = lo;
             }
         }
-        dbr += sr;
-        dbi += si;
-        dl += sl;
+        total += (double)row_sums(sr, si, sl, dcb);
         if (s == 0 && rho == 0 && P.dh0) P.dh0[b * D + ch] = carry;
     };
 
@@ -648,9 +657,8 @@ __global__ __launch_bounds__(NT, 2) void fused_bwd_kernel(Params P) {
                                                        fmaf(wt[2], dc[i + 2], wt[3] * dc[i + 3]))));
             }
             wave_fence();  // stage() overwrites the steps that other lanes read here
-            dcb += sb;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) dcw[j] += sw[j];
+            dcb = sb;  // joins `total` with the next tile's sums
+            total_w += (double)row_sums(sw[0], sw[1], sw[2], sw[3]);
         }
     };
 
@@ -810,7 +818,6 @@ __global__ __launch_bounds__(NT, 2) void fused_bwd_kernel(Params P) {
 
     // ---- this workgroup's partial sums
     const int rho = lane >> 4, ch = 16 * w + (lane & 15);
-    const bool odd = rho & 1, upper = rho >= 2;
     float* const pw = P.part_w + (int64_t)blockIdx.x * 2 * D * D;
 #pragma unroll
     for (int u = 0; u < 2; ++u)
@@ -823,27 +830,11 @@ __global__ __launch_bounds__(NT, 2) void fused_bwd_kernel(Params P) {
                 pw[row * D + col] = dw[u][c][v];
             }
     float* const pc = P.part_c + (int64_t)blockIdx.x * G::kCols * D;
-    auto fold = [&](float v) {  // the four lanes of a channel, in a fixed order
-        const float q = row_partner(v, odd);
-        const float two = odd ? q + v : v + q;
-        const float r = half_partner(two, upper);
-        return upper ? r + two : two + r;
-    };
-    const float fr = fold(dbr), fi = fold(dbi), fl = fold(dl);
-    if (rho == 0) {
-        pc[ch] = fr;
-        pc[D + ch] = fi;
-        pc[2 * D + ch] = fl;
-    }
     if constexpr (GATE) {
-        const float fb = fold(dcb);
-        if (rho == 0) pc[3 * D + ch] = fb;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const float f = fold(dcw[j]);
-            if (rho == 0) pc[(4 + j) * D + ch] = f;
-        }
+        total += (double)row_sums(0.0f, 0.0f, 0.0f, dcb);
+        pc[(4 + rho) * D + ch] = (float)total_w;
     }
+    if (GATE || rho < 3) pc[rho * D + ch] = (float)total;
 }
 
 // The weights in fragment order, as bf16 hi and lo planes (bf16 weights: one).

@@ -301,6 +301,40 @@ def test_full_backward_one_kernel(rb, rows, io, state):
             assert_close(host(v), want[k], io, k)
 
 
+# Sums over many rows in the one-kernel backward: the same row 25600 times, 100 to a
+# workgroup, against 256 times, one to a workgroup.  A row's tile gives one fp32 part, parts
+# add up in double, a workgroup's sum and the result are rounded to fp32: each result is
+# 100 times the other's up to three roundings (2^-24 of the value).
+@pytest.mark.parametrize("case", ["layer_f32", "layer_bf16", "gated_f32"])
+def test_one_kernel_backward_sums_over_rows(rb, case):
+    kind, io = case.split("_")
+    L, D = 64, 128
+    f = dg.full_inputs(1, L, D, 6100, io=io, bias=True, h0=True, grad=True)
+    rng = np.random.Generator(np.random.PCG64(6101))
+    Wr, br, Wi, bi = (dev(a, io) for a in (f.Wr, f.br, f.Wi, f.bi))
+    lam = dev32(f.lam)
+    if kind == "gated":
+        hz, w, cb = (dev32(rng.standard_normal(n, dtype=np.float32))
+                     for n in ((1, L, D), (D, 4), (D,)))
+    got = []
+    for B in (256, 25600):
+        rows = lambda t: t.expand(B, *t.shape[1:]).contiguous()  # noqa: E731,B023
+        x, dh, h0 = rows(dev(f.x, io)), rows(dev(f.dh, io)), rows(dev32(f.h0))
+        if kind == "layer":
+            args = (x, Wr, br, Wi, bi, lam)
+            got.append(rb.bdlru_backward(*args, rb.bdlru_forward(*args, h0)[0], dh, h0))
+        else:
+            args = (x, rows(hz), w, cb, Wr, br, Wi, bi, lam)
+            got.append(rb.gated_backward(*args, rb.gated_forward(*args, h0)[1], dh, h0))
+    print(f"sums over rows {case}: GPU done", flush=True)
+    names = ["dbr", "dbi", "dlambda"] + (["dconv_w", "dconv_b"] if kind == "gated" else [])
+    for k in names:
+        want, many = 100.0 * got[0][k].double(), got[1][k].double()
+        err = ((many - want).abs() / want.abs()).max().item()
+        print(f"{case} {k}: {err:.3e}", flush=True)
+        assert err <= 3.01 * 2.0 ** -24, (k, err)
+
+
 # Both gradient products of the projections in one pass over dz: 32-row tiles and
 # ranges of at least 256 rows; one part-filled tile, one whole one, a range's edge,
 # ranges of unequal length, and 16384 rows, where fp32 x takes it at D = 192 too.
