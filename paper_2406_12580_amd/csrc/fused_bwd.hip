@@ -942,14 +942,25 @@ bool fused2_backward_applies(int64_t B, int64_t L, int64_t D, IoType io, const v
     if (D != fbw::D || B <= 0 || L <= 0 || (gated && io != IoType::kF32)) return false;
     if (((uintptr_t)x | (uintptr_t)h | (uintptr_t)dx) % 16 != 0) return false;
     if ((L + fbw::TS) * D * (int64_t)io_bytes(io) >= ((int64_t)1 << 31)) return false;
-    // A workgroup walks whole rows, so the kernel takes rounds of 256 rows however
-    // few the last one holds: about 0.2 us per round and step (fp32; 0.13 us bf16)
-    // and three launches, against 1.4 ns (1.0 ns) per row and step and eight
-    // launches for the separate kernels.  Layer forward + backward, 512 steps, us:
-    // B = 96: 160 -> 144 (bf16 128 -> 111), 192: 240 -> 178 (185 -> 129), 300: 347 -> 283
-    // (252 -> 211).
-    const int64_t rounds = (B + fbw::kMaxGroups - 1) / fbw::kMaxGroups;
-    return (128 * rounds - B) * L <= 20000;
+    // A workgroup walks whole rows, 256 of them in a round, and a step of a round takes
+    // 0.16 us (fp32; gated 0.22, bf16 0.12) with few rows and 0.22 (0.30, 0.16) with all
+    // 256; the separate kernels take 1.32 ns (1.99, 0.98) a row and step and 5 to 20 us
+    // more for their launches.  So a part-filled last round pays from about 142 rows on, a
+    // full round before it makes up for 110 rows of that, and the launches for
+    // kSaved row-steps (steps in whole tiles).  Backward, separate kernels -> this one, us
+    // (fp32 layer / bf16 layer / gated):
+    //   rows x steps   taken                                     not taken
+    //   32 x 64        32 -> 27, 30 -> 28, 69 -> 29
+    //   32 x 200       -, -, 78 -> 65                            38 -> 50, 36 -> 41
+    //   128 x 1024     203 -> 187, 153 -> 144, 308 -> 265
+    //   128 x 8192     -                                         1427 -> 1480, 1049 -> 1114, 2084 -> 2105
+    //   256 x 2048     691 -> 459, 514 -> 338, 1044 -> 612
+    //   257 x 2048     -                                         718 -> 780, 530 -> 594, 1053 -> 1065
+    //   300 x 2048     844 -> 795, 624 -> 598, 1237 -> 1088
+    const int64_t rows = B % fbw::kMaxGroups, rounds = B / fbw::kMaxGroups;
+    const int64_t steps = (L + fbw::TS - 1) / fbw::TS * fbw::TS;
+    const int64_t kSaved = gated ? 34000 : io == IoType::kF32 ? 14400 : 16200;
+    return rows == 0 || (142 - rows - 110 * rounds) * steps <= kSaved;
 }
 
 size_t fused2_backward_workspace(int64_t B, int64_t L, int64_t D) {

@@ -265,8 +265,12 @@ def test_full_backward_fused(rb, shape, io):
 
 
 # The one-kernel layer backward (D = 128): steps at the edges of its 64-step
-# tiles and 32-step blocks, one tile and several, more rows than workgroups.
-ONE_KERNEL_BWD = [(3, 1), (2, 32), (3, 33), (2, 64), (3, 65), (2, 96), (1, 150), (300, 70)]
+# tiles and 32-step blocks, one tile and several, more rows than workgroups.  Few rows of
+# several tiles take the separate kernels: in fp32 up to 29 rows of two tiles and 66 of
+# three.
+ONE_KERNEL_BWD = [(3, 1), (2, 32), (3, 33), (2, 64), (3, 65), (2, 96), (1, 150), (300, 70),
+                  (29, 65), (30, 65), (30, 96), (66, 129), (67, 129), (67, 150), (256, 193),
+                  (257, 128), (513, 65)]
 
 
 @pytest.mark.parametrize("state", [False, True])
