@@ -124,13 +124,19 @@ __device__ __forceinline__ void tile_z(const T* x, const __bf16* pack, const TW*
     float* zs = (float*)smem + w * 64 * ZP;
     const ElemReader<TW> rbr(br, D), rbi(bi, D);
     const int64_t d = cg * kWave + (lane & 15);
+    float bias[2][4];  // read ahead of the fences
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        bias[0][j] = rbr(d + 16 * j);
+        bias[1][j] = rbi(d + 16 * j);
+    }
 #pragma unroll
     for (int gate = 0; gate < 2; ++gate) {
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const int col = 16 * j + (lane & 15);
-            const float bias = gate == 0 ? rbr(d + 16 * j) : rbi(d + 16 * j);
-            *(f4*)&zs[col * ZP + 4 * (lane >> 4)] = acc[4 * gate + j] + f4{bias, bias, bias, bias};
+            const float v = bias[gate][j];
+            *(f4*)&zs[col * ZP + 4 * (lane >> 4)] = acc[4 * gate + j] + f4{v, v, v, v};
         }
         wave_fence();
         float* dst = gate == 0 ? zr : zi;
