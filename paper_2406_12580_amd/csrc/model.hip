@@ -931,16 +931,18 @@ Layout layout(const Dims& d) {
         at += align_up(bytes);
         return o;
     };
-    w.H = take((size_t)((L + 1) * M * D) * f);  // layer inputs / outputs
+    const int64_t R = (L - 1) * M + d.B;  // rows of every layer; of the last one the last steps
+    w.H = take((size_t)((M + R) * D) * f);  // layer inputs / outputs
     w.Hx = take((size_t)(L * M * ED) * f);
     w.Hz = take((size_t)(L * M * ED) * f);
     w.hb = take((size_t)(L * M * ED) * f);      // BD-LRU outputs
     w.y = take((size_t)(L * M * ED) * f);
-    w.s1 = take((size_t)(L * M * D) * f);
-    w.H1 = take((size_t)(L * M * D) * f);
-    w.A = take((size_t)(L * M * F) * f);
-    w.P = take((size_t)(L * M * F) * f);
-    w.s2 = take((size_t)(L * M * D) * f);
+    w.s1 = take((size_t)(R * D) * f);
+    w.H1 = take((size_t)(R * D) * f);
+    w.A = take((size_t)(R * F) * f);
+    // (the one-kernel feed-forward of D = 64 keeps SiLU(A) and its gradient on chip)
+    if (D != 64) w.P = take((size_t)(R * F) * f);
+    w.s2 = take((size_t)(R * D) * f);
     w.stats = take((size_t)(L * 4 * M) * f);    // mean and 1/std of both LayerNorms
     w.emb_stats = take((size_t)(2 * M) * f);
     w.logits = take((size_t)(d.B * d.V) * f);
@@ -949,7 +951,7 @@ Layout layout(const Dims& d) {
     w.X = take((size_t)(M * D) * f);
     w.Y = take((size_t)(M * D) * f);
     w.Z = take((size_t)(M * D) * f);            // a sub-layer output's gradient (dropout)
-    w.dP = take((size_t)(M * F) * f);
+    if (D != 64) w.dP = take((size_t)((L > 1 ? M : d.B) * F) * f);
     w.dY = take((size_t)(M * ED) * f);
     w.dHx = take((size_t)(M * ED) * f);
     w.dHz = take((size_t)(M * ED) * f);
@@ -989,7 +991,8 @@ Layout layout(const Dims& d) {
     w.emb_np = take((size_t)(d.V + 1) * sizeof(int64_t));
     w.emb_poff = take((size_t)(d.V + 1) * sizeof(int64_t));
     w.emb_part = take((size_t)(max_pieces * D) * f);
-    w.mask = take((size_t)(mask_sites(d) * mask_words(d)) * sizeof(uint32_t));
+    w.mask = take((size_t)((mask_sites(d) - 2) * mask_words(d) + 2 * d.B * (D / 32)) *
+                  sizeof(uint32_t));  // the last layer's two sites: last steps only
     w.pos_s = take((size_t)M * sizeof(int));
     if (d.V <= kCountKeys) {
         // the runs' counts, then the items' totals
@@ -1234,7 +1237,8 @@ int train_step_t(const Dims& d, const StepOpts& o, const float* params, const in
     // The linear sub-layers in one kernel each way, where their rows are 64 wide.  Each
     // one's parameters (and gradients) lie one after the other without padding: their
     // sizes are multiples of 64 floats.
-    const bool ffn_fused = sublayers_fused_applies(M, D, {ws, params, grads});
+    const bool ffn_fused = D == 64;  // (the layout has no room for the other path's P and dP)
+    CHECK(!ffn_fused || sublayers_fused_applies(M, D, {ws, params, grads}));
     const bool proj_fused = ffn_fused && ED == 128;
 
     // ---- forward

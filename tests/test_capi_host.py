@@ -264,6 +264,27 @@ def test_model_validation(rb):
 
 
 
+def test_model_workspace_holds_what_is_used(rb):
+    """Workspace a layer adds and of one layer, D = 64: what the backward reads again of every
+    step (the last layer's row-wise part: of the last step only), and no tensor of hidden
+    units but the one kept for the backward."""
+    import ctypes
+    B, T, D, ED, F = 2048, 200, 64, 128, 256
+    M = B * T
+    one, two = (rb.recblr_model_workspace_size(ctypes.byref(rb.model_dims(B, T, D, layers=n)))
+                for n in (1, 2))
+    partials = 2 * 2 * -(-M // 64) * D  # LayerNorm gradients: one row per 64 rows at most
+    layer = M * (D + 4 * ED + 3 * D + F + 4) + 2 * M * D // 32 + partials
+    assert two - one <= 4 * layer + 64 * 256
+    gated = max(rb.recblr_workspace_size(op, B, T, ED, rb.F32)
+                for op in (rb.OP_GATED_FORWARD, rb.OP_GATED_BACKWARD))
+    # input, the gated layer's four tensors, three gradients each of width D and ED, ids sorted,
+    # statistics; the prediction's B V floats and at most 128 MiB of partial sums
+    steps = 4 * M * (D + 4 * ED + 3 * D + 3 * ED + 1 + 2 + 4 + 2)
+    small = 4 * 2 * B * 3416 + (128 << 20)
+    assert one <= steps + gated + small
+
+
 def test_noalloc_rejects_problems_beyond_its_static_scratch(rb):
     """256 x 65536 x 128 fp32 needs ~200 MiB of look-back state and dLambda
     partials, past the 16 MiB static array: rejected before any HIP call."""
