@@ -148,18 +148,6 @@ __device__ __forceinline__ void stage_tile(const T* x, int64_t b, int64_t L, int
     }
 }
 
-// x of (local row r, input k) from the LDS tile.
-template <typename T, int D>
-__device__ __forceinline__ float tile_x(const char* buf, int r, int k) {
-    if constexpr (sizeof(T) == 2) {
-        const int off = r * (D * 2) + (((k >> 3) ^ swz16(r)) << 4) + (k & 7) * 2;
-        return __uint_as_float((uint32_t)(*(const uint16_t*)(buf + off)) << 16);
-    } else {
-        const int off = r * (D * 4) + (((k >> 2) ^ swz32(r)) << 4) + (k & 3) * 4;
-        return *(const float*)(buf + off);
-    }
-}
-
 // fp32 I/O: split the raw tile into bf16 hi and lo operand planes.
 template <int D, int NT>
 __device__ __forceinline__ void split_tile(const char* raw, char* planes, int tid) {
@@ -288,8 +276,6 @@ __device__ __forceinline__ void conv_tile(const char* hxb, const float* taps, ch
         }
     }
 }
-
-__device__ __forceinline__ float sw_bits(uint32_t v) { return __uint_as_float(v); }
 
 // v_permlane16_swap of two accumulators: even 16-lane rows keep a and get
 // b's... see the exchange in the kernel.

@@ -22,7 +22,7 @@
 //    gradient is split over rows into about two workgroups per CU, its fp32
 //    partials summed afterwards in a fixed order (deterministic), db summed
 //    from the same staged dz rows.  The same engine packs the weights for the
-//    fused scans (pack_group_kernel) and runs the decode step's product
+//    fused scans (prepare_kernel) and runs the decode step's product
 //    (step_kernel), and its fp32 linear32 / wgrad kernels serve the model
 //    step's linear layers.
 //  * the generic kernels (proj_*_kernel), for D % 8 != 0 or unaligned
@@ -541,23 +541,6 @@ __global__ __launch_bounds__(256) void prepare_kernel(const T* wr, const T* wi, 
     }
     if (e < 2) ticket[e] = 0u;  // ticket, status
     for (int64_t k = e; k < n; k += (int64_t)gridDim.x * blockDim.x) states[k] = ~0ull;
-}
-
-// Weights ordered by channel group for the scan forward with the projections
-// fused in: rows 128 g .. 128 g + 63 are W_r rows of channels 64 g .. 64 g + 63,
-// the next 64 rows the W_i rows of the same channels (D % 64 == 0).
-template <typename T>
-__global__ __launch_bounds__(256) void pack_group_kernel(const T* wr, const T* wi, __bf16* out,
-                                                         int64_t D) {
-    const int64_t total = 2 * D * D;
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= total) return;
-    const int64_t n = e / D, k = e % D;
-    const int64_t ch = (n / 128) * 64 + n % 64;
-    const float v = (n / 64) % 2 == 0 ? to_f32(wr[ch * D + k]) : to_f32(wi[ch * D + k]);
-    const __bf16 hi = (__bf16)v;
-    out[e] = hi;
-    if (sizeof(T) == 4) out[total + e] = (__bf16)(v - (float)hi);
 }
 
 template <typename T>
