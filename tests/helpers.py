@@ -71,3 +71,38 @@ def dev32(a):
 def host(t):
     import torch
     return t.detach().to(torch.float32).cpu().numpy()
+
+
+def gated_backward_from_h(hx, hz, conv_w, Wr, br, Wi, bi, lam, h, dy):
+    """Gradients of the gated layer (zero initial state, no conv bias) in numpy's 64 bits, as
+    the oracle's gated_backward but from a given h instead of one formed again: the
+    reference of a backward that reads an h rounded to bf16."""
+    hx, hz, conv_w, Wr, br, Wi, bi, lam, h, dy = (
+        np.asarray(a, dtype=np.float64) for a in (hx, hz, conv_w, Wr, br, Wi, bi, lam, h, dy))
+    B, L, D = hx.shape
+    K = conv_w.shape[1]
+    sig = lambda v: 1.0 / (1.0 + np.exp(-v))  # noqa: E731
+    c = np.zeros_like(hx)
+    for j in range(min(K, L)):
+        c[:, j:] += conv_w[:, j] * hx[:, :L - j]
+    sc, sz = sig(c), sig(hz)
+    x = c * sc
+    r, i = sig(x @ Wr.T + br), sig(x @ Wi.T + bi)
+    sp = np.log1p(np.exp(lam))
+    a, m = np.exp(-sp * r), np.sqrt(-np.expm1(-2.0 * sp * r))
+    delta = dy * hz * sz
+    for t in range(L - 2, -1, -1):
+        delta[:, t] += a[:, t + 1] * delta[:, t + 1]
+    hp = np.concatenate([np.zeros((B, 1, D)), h[:, :-1]], axis=1)
+    dq = delta * (x * i * a * a / m - a * hp)
+    dzr, dzi = sp * dq * r * (1 - r), delta * x * m * i * (1 - i)
+    dc = (delta * m * i + dzr @ Wr + dzi @ Wi) * sc * (1 + c * (1 - sc))
+    out = {"dhz": dy * h * sz * (1 + hz * (1 - sz)), "dlambda": sig(lam) * (dq * r).sum((0, 1)),
+           "dhx": np.zeros_like(hx), "dconv_w": np.zeros_like(conv_w)}
+    for j in range(min(K, L)):
+        out["dhx"][:, :L - j] += conv_w[:, j] * dc[:, j:]
+        out["dconv_w"][:, j] = (dc[:, j:] * hx[:, :L - j]).sum((0, 1))
+    for k, dz in (("r", dzr), ("i", dzi)):
+        out["dW" + k] = dz.reshape(-1, D).T @ x.reshape(-1, D)
+        out["db" + k] = dz.sum((0, 1))
+    return out

@@ -143,14 +143,21 @@ def test_model_train_step_dropout_padding(rb, case):
     step.close()
 
 
-# The one-kernel sub-layers of D = 64: 32-row tiles and ranges of at least 256 rows; one
-# part-filled tile, one whole one, one row past it, a range's edge.  Without dropout
-# the feed-forward backward reads and accumulates in the same buffer.
+# The one-kernel sub-layers of D = 64: tiles of 32 rows in ranges of whole tiles.  With one
+# layer the feed-forward and the output projection see the B last steps only, with two the
+# lower layer's see all B T rows: one part-filled tile, a whole one, one row past it, a range
+# for each tile; then ranges of several tiles with a part-filled last one in every kernel
+# (32900 rows: 5 tiles, 3 for the output projection, the forward's workgroups 4 or 5).
+# Without dropout the feed-forward backward reads and accumulates in the same buffer.
+SUBLAYER_ROWS = [(1, 7, 1), (2, 16, 1), (3, 11, 1), (1, 257, 1), (19, 54, 1), (33, 5, 1),
+                 (1, 7, 2), (2, 16, 2), (3, 11, 2), (1, 257, 2), (165, 100, 2), (235, 140, 2)]
+
+
 @pytest.mark.parametrize("p", [0.0, 0.2])
-@pytest.mark.parametrize("rows", [(1, 7), (2, 16), (3, 11), (1, 257), (19, 54)])
+@pytest.mark.parametrize("rows", SUBLAYER_ROWS)
 def test_model_one_kernel_sublayers(rb, rows, p):
     import torch
-    dims = dg.ModelDims(B=rows[0], T=rows[1], D=64, E=2, V=50, layers=1, K=4, eps=1e-5)
+    dims = dg.ModelDims(B=rows[0], T=rows[1], D=64, E=2, V=50, layers=rows[2], K=4, eps=1e-5)
     named = dg.model_params(dims, 970 + rows[1])
     ids, targets = dg.model_batch(dims, 980 + rows[1])
     rd, P, _ = _device_params(rb, dims, named)

@@ -12,7 +12,8 @@ import numpy as np
 import pytest
 
 import oracle
-from helpers import TOL, assert_close, dev, dev32, floored_rel_err, host, report
+from helpers import (TOL, assert_close, dev, dev32, floored_rel_err, gated_backward_from_h, host,
+                     report)
 from paper_2406_12580_amd import datagen as dg
 
 pytestmark = pytest.mark.gpu
@@ -339,16 +340,20 @@ def test_one_kernel_backward_sums_over_rows(rb, case):
         assert err <= 3.01 * 2.0 ** -24, (k, err)
 
 
-# Both gradient products of the projections in one pass over dz: 32-row tiles and
-# ranges of at least 256 rows; one part-filled tile, one whole one, a range's edge,
-# ranges of unequal length, and 16384 rows, where fp32 x takes it at D = 192 too.
+# Both gradient products of the projections in one pass over dz: 32-row tiles in ranges of
+# at least two, at most 512, 256, 128 and 128 ranges (D = 64 to 256); one part-filled tile, one
+# whole one, a range's edge, ranges of unequal length; 16384 rows, where fp32 x takes it at
+# D = 192 too; and for each width a range of several tiles (the two tile buffers reused) and
+# a part-filled last one.  3 rows of that many steps miss the one-kernel backward of D = 128.
+BOTH_PRODUCTS = [(r, D) for D in (64, 128, 192, 256)
+                 for r in [(3, 7), (1, 32), (2, 128), (3, 257)]] + [
+    ((128, 129), 192), ((3, 10967), 64), ((3, 5495), 128), ((3, 5510), 192), ((3, 2774), 256)]
+
+
 @pytest.mark.parametrize("io", ["f32", "bf16"])
-@pytest.mark.parametrize("D", [64, 128, 192, 256])
-@pytest.mark.parametrize("rows", [(3, 7), (1, 32), (2, 128), (3, 257), (128, 129)])
+@pytest.mark.parametrize("rows,D", BOTH_PRODUCTS)
 def test_full_backward_both_products(rb, rows, D, io):
     B, L = rows
-    if B * L > 16000 and D != 192:
-        pytest.skip("only D = 192 depends on the row count")
     f = dg.full_inputs(B, L, D, 4900 + B + L + D, io=io, bias=True, grad=True)
     X, Wr, br, Wi, bi = (dev(a, io) for a in (f.x, f.Wr, f.br, f.Wi, f.bi))
     lam = dev32(f.lam)
@@ -373,11 +378,8 @@ def test_full_backward_both_products(rb, rows, D, io):
     else:
         # The backward reads the h that was stored in bf16.  That rounding (2^-9 of h, in
         # a dz that is a difference) stays whole in the dW of one row of 32 steps: 1.6e-2
-        # there against the oracle, whose h is exact.  So the oracle's part is taken by
-        # the fp32 entry, checked against it above, on the same numbers and the same h.
-        wide = [None if a is None else a.float() for a in args]
-        want = {k: None if v is None else host(v)
-                for k, v in rb.gated_backward(*wide, h.float(), dev(f.dh)).items()}
+        # there against the oracle, whose h is exact.  So the reference starts from that h.
+        want = gated_backward_from_h(f.x, hz, w, f.Wr, f.br, f.Wi, f.bi, f.lam, host(h), f.dh)
     for k in ("dhx", "dhz", "dconv_w", "dWr", "dbr", "dWi", "dbi", "dlambda"):
         assert_close(host(got[k]), want[k], io, k)
 

@@ -22,6 +22,7 @@ import pytest
 from scipy.special import expit
 
 import oracle
+from helpers import gated_backward_from_h
 from paper_2406_12580_amd import datagen as dg
 
 GOLDEN = os.path.join(os.path.dirname(__file__), "golden")
@@ -622,3 +623,18 @@ def test_gated_backward_adjoint_dot_product():
     names = ("dhx", "dhz", "dconv_w", "dconv_b", "dWr", "dbr", "dWi", "dbi", "dlambda", "dh0")
     jtg = sum(float(np.sum(got[k] * u)) for k, u in zip(names, v))
     assert abs(jv - jtg) <= 1e-7 * max(1.0, abs(jv))
+
+
+@pytest.mark.parametrize("shape", [(3, 7, 5, 4), (1, 1, 3, 2), (2, 40, 16, 1)])
+def test_gated_backward_from_its_own_h(shape):
+    """The numpy reference that starts from a given h, given the oracle's: its gradients."""
+    B, L, D, K = shape
+    f = dg.full_inputs(B, L, D, 77, bias=True, grad=True)
+    rng = np.random.Generator(np.random.PCG64(78))
+    hz, w = rng.standard_normal((B, L, D)), rng.standard_normal((D, K))
+    args = (f.x, hz, w, None, f.Wr, f.br, f.Wi, f.bi, f.lam)
+    _, h, _ = oracle.gated_forward(*args)
+    want = oracle.gated_backward(*args, f.dh)
+    got = gated_backward_from_h(f.x, hz, w, f.Wr, f.br, f.Wi, f.bi, f.lam, h, f.dh)
+    for k, v in got.items():
+        np.testing.assert_allclose(v, want[k], rtol=1e-9, atol=1e-12, err_msg=k)
