@@ -426,8 +426,8 @@ int recblr_bdlru_forward(const void* x, const void* W_r, const void* b_r, const 
                                                nullptr, B, L, D, io_of(io), at(ws, lay.scan),
                                                strm));
     if (L > 0 && fused_forward_applies(B, L, D, io_of(io), x, pack)) {
-        return status_of(launch_fused_forward(x, W_r, W_i, pack, b_r, b_i, lambda, h0, h, hT, B, L, D,
-                                              io_of(io), at(ws, lay.scan), strm));
+        return status_of(launch_fused_forward(x, W_r, W_i, pack, b_r, b_i, lambda, h0, h, hT, B, L,
+                                              D, io_of(io), at(ws, lay.scan), strm));
     }
     hipError_t e = launch_project_forward(x, W_r, b_r, W_i, b_i, zr, zi, B * L, D, io_of(io),
                                           pack, strm);
@@ -483,8 +483,9 @@ int recblr_gated_forward(const void* hx, const void* hz, const float* conv_w,
     if (launch_conv_silu(hx, w4, b4, xp, B, L, D, io_of(io), io_of(io), strm) != hipSuccess)
         return RECBLR_ERR_HIP;
     if (L > 0 && fused_forward_applies(B, L, D, io_of(io), xp, pack)) {
-        return status_of(launch_fused_gated_forward(xp, hz, W_r, W_i, pack, b_r, b_i, lambda, h0, y, h, hT,
-                                                    B, L, D, io_of(io), fws + fl.scan, strm));
+        return status_of(launch_fused_gated_forward(xp, hz, W_r, W_i, pack, b_r, b_i, lambda, h0,
+                                                    y, h, hT, B, L, D, io_of(io), fws + fl.scan,
+                                                    strm));
     }
     // Otherwise the layer forward on x', then the gate.
     void* hout = h ? h : at(ws, lay.hbuf);

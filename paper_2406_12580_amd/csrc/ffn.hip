@@ -33,10 +33,13 @@
 #include "device_common.hpp"
 #include "launch.hpp"
 #include "mfma_tile.hpp"
+#include "wave_tile.hpp"
 #include "gemm.hpp"
 
 namespace recblr {
 namespace ffn {
+
+using namespace wtile;
 
 constexpr int D = 64, F = 256, TR = 32, NW = 8, NT = NW * kWave;
 constexpr int kPlane = TR * D * 2;                 // bytes of a plane of a row tile
@@ -45,40 +48,10 @@ constexpr int kTrans = 32 * 32 * 2;                // a plane of a wave's dA blo
 constexpr int64_t kPart = kFfnGrads;               // [dW1 | db1 | dW2 | db2]
 static_assert(kPart == 2 * F * D + F + D);
 
-typedef float f16v __attribute__((ext_vector_type(16)));
-typedef float f4 __attribute__((ext_vector_type(4)));
-typedef __bf16 b8 __attribute__((ext_vector_type(8)));
-typedef short s4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u4v __attribute__((ext_vector_type(4)));
-typedef uint32_t u2v __attribute__((ext_vector_type(2)));
-typedef __attribute__((address_space(3))) s4 lds_s4;
-
 // Chunk j (16 bytes of 128) of row r of a plane at j ^ swz(r): 16 rows of one chunk,
 // and 4 rows of 4 chunks, land on distinct banks.
 __device__ __forceinline__ int swz(int r) { return ((r >> 1) & 1) << 2 | ((r >> 2) & 3); }
 
-__device__ __forceinline__ void lds_barrier() {
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0); vector memory stays in flight
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-}
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const void* p, uint32_t bytes) {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, (int)bytes,
-                                             0x00020000);
-}
-__device__ __forceinline__ int fresh(int lane) {
-    asm volatile("" : "+v"(lane));  // addresses are formed again in each tile, not kept
-    return lane;
-}
-__device__ __forceinline__ b8 tr_pair(const char* p0, const char* p1) {
-    const s4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4*)p0);
-    const s4 c = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4*)p1);
-    return __builtin_bit_cast(b8, __builtin_shufflevector(a, c, 0, 1, 2, 3, 4, 5, 6, 7));
-}
-__device__ __forceinline__ f16v mfma(b8 a, b8 b, f16v c) {
-    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
-}
 // Planes 0 (high) to 2 of both: the products above 2^-27 of the full one.
 __device__ __forceinline__ f16v mma6(const b8 (&a)[3], const b8 (&b)[3], f16v c) {
     c = mfma(a[1], b[1], c);
@@ -796,7 +769,8 @@ constexpr int kBwdSmem = 2 * 5 * kPlane + NW * 3 * kTrans + kExch;
 
 template <typename K>
 hipError_t allow_lds(K kern, int bytes) {
-    return hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+    return hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
+                               bytes);
 }
 
 // `most` workgroups (one or two per compute unit), a tile or more each: every range

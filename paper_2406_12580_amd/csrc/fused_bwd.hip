@@ -56,21 +56,17 @@
 #include "device_common.hpp"
 #include "launch.hpp"
 #include "mfma_tile.hpp"
+#include "wave_tile.hpp"
 
 namespace recblr {
 namespace fbw {
+
+using namespace wtile;
 
 constexpr int D = 128;            // channels
 constexpr int TS = 64;            // steps per tile
 constexpr int NW = 8;             // waves per workgroup
 constexpr int NT = NW * kWave;
-
-typedef float f16v __attribute__((ext_vector_type(16)));
-typedef __bf16 b8 __attribute__((ext_vector_type(8)));
-typedef short s4 __attribute__((ext_vector_type(4)));
-typedef short s8 __attribute__((ext_vector_type(8)));
-typedef uint32_t u4v __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) s4 lds_s4;
 
 struct Params {
     const void* x;        // [B][L][D] TX: x, or hx (GATE)
@@ -108,33 +104,6 @@ __device__ __forceinline__ int swz16(int r) {
 }
 __device__ __forceinline__ int swz32(int r) { return (((r >> 3) & 3) << 2) ^ ((r << 1) & 8); }
 __device__ __forceinline__ int swzdz(int r) { return ((r & 2) << 1) | ((r >> 2) & 3); }
-// A-operand row of MFMA row R: lane half h of the accumulator then holds steps
-// 16 h .. 16 h + 15 of the block in VGPRs 0 .. 15.
-__device__ __forceinline__ int sigma(int R) { return 16 * ((R >> 2) & 1) + 4 * (R >> 3) + (R & 3); }
-
-__device__ __forceinline__ void lds_barrier() {
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0); vector memory stays in flight
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-}
-
-__device__ __forceinline__ void swap16(float& a, float& b) {
-    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false,
-                                                    false);
-    a = __uint_as_float(r[0]);
-    b = __uint_as_float(r[1]);
-}
-__device__ __forceinline__ float row_partner(float v, bool odd) {
-    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false,
-                                                    false);
-    return __uint_as_float(odd ? r[0] : r[1]);
-}
-__device__ __forceinline__ float half_partner(float v, bool upper) {
-    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false,
-                                                    false);
-    return __uint_as_float(upper ? r[0] : r[1]);
-}
 
 // Four values summed over the four 16-lane rows of the wave: row r gets value r's sum.
 __device__ __forceinline__ float row_sums(float a, float b, float c, float d) {
@@ -145,11 +114,6 @@ __device__ __forceinline__ float row_sums(float a, float b, float c, float d) {
     const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(c), false,
                                                     false);
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const void* p, uint32_t bytes) {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, (int)bytes,
-                                             0x00020000);
 }
 
 // One element through a buffer resource (reads past it give 0).
@@ -168,43 +132,18 @@ __device__ __forceinline__ void bstore(__amdgpu_buffer_rsrc_t r, uint32_t off, f
         __builtin_amdgcn_raw_buffer_store_b16(from_f32<bf16>(v).bits, r, off, 0, 0);
 }
 
-// 8 consecutive-k values of an MFMA operand whose k runs across LDS rows:
-// a transposing read hands lane i of each 16-lane block column i of a 4-row x
-// 16-column block whose row j the lanes 4 j .. 4 j + 3 address.
-__device__ __forceinline__ b8 tr_pair(const char* p0, const char* p1) {
-    const s4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4*)p0);
-    const s4 c = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4*)p1);
-    return __builtin_bit_cast(b8, __builtin_shufflevector(a, c, 0, 1, 2, 3, 4, 5, 6, 7));
-}
-
 template <typename TX, typename TW, bool GATE>
 struct Geo {
     static constexpr bool kXf32 = sizeof(TX) == 4;
     static constexpr int PX = kXf32 ? 2 : 1;             // x planes
     static constexpr int PW = sizeof(TW) == 4 ? 2 : 1;   // W planes
     static constexpr int kXPlane = TS * D * 2;
-    static constexpr int kRaw = TS * D * 4;              // fp32 tile: x (fp32 I/O), then dx's direct term
+    static constexpr int kRaw = TS * D * 4;  // fp32 tile: x (fp32 I/O), then dx's direct term
     static constexpr int kDzPlane = 2 * D * TS * 2;
     static constexpr int kSmem = PX * kXPlane + (GATE ? 2 : 1) * kRaw + 2 * kDzPlane;
     static constexpr int kCols = GATE ? 3 + 1 + kConvTaps : 3;  // columns of part_c
     static constexpr int kXLoads = TS * D * (int)sizeof(TX) / (NT * 16);  // 16-byte loads a thread
 };
-
-// The lane index, recomputed where it is used: LDS addresses derived from it
-// are formed again in each tile (a few vector instructions) instead of being
-// kept in registers across the whole loop.
-__device__ __forceinline__ int fresh(int lane) {
-    asm volatile("" : "+v"(lane));
-    return lane;
-}
-
-// One product term set: acc += a b with the planes each operand has.
-template <int PA, int PB>
-__device__ __forceinline__ f16v mma(const b8 (&a)[PA], const b8 (&b)[PB], f16v acc) {
-    if constexpr (PB == 2) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], b[1], acc, 0, 0, 0);
-    if constexpr (PA == 2) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[1], b[0], acc, 0, 0, 0);
-    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], b[0], acc, 0, 0, 0);
-}
 
 template <typename TX, typename TH, typename TW, bool GATE>
 __global__ __launch_bounds__(NT, 2) void fused_bwd_kernel(Params P) {
@@ -214,7 +153,7 @@ __global__ __launch_bounds__(NT, 2) void fused_bwd_kernel(Params P) {
     static_assert(!GATE || (EX == 4 && EH == 4 && PW == 2), "the gated layer's backward is fp32");
     extern __shared__ __attribute__((aligned(16))) char smem[];
     char* const xpl = smem;                       // x planes [PX][TS][D], GATE [PX][D][TS]
-    char* const raw = smem + PX * G::kXPlane;     // fp32 [TS][D]: x (fp32 I/O), then dx's direct term
+    char* const raw = smem + PX * G::kXPlane;     // fp32 [TS][D]: x, then dx's direct term
     char* const dzp = raw + G::kRaw;              // dz planes [2][2 D][TS]
     char* const hxt = dzp + 2 * G::kDzPlane;      // GATE: fp32 [TS][D], hx
 
@@ -875,7 +814,6 @@ __global__ __launch_bounds__(256) void reduce_kernel(const float* __restrict__ p
                                                      float* dwi, float* dbr, float* dbi,
                                                      float* dlambda, int cols, float* dcw,
                                                      float* dcb, int K) {
-    typedef float f4 __attribute__((ext_vector_type(4)));
     constexpr int kCols = 16, kGroups = 16;  // 16 x 4 columns a block, 16 row groups
     __shared__ double red[kGroups][kCols * 4];
     const int c = threadIdx.x % kCols, g = threadIdx.x / kCols;
@@ -949,13 +887,13 @@ bool fused2_backward_applies(int64_t B, int64_t L, int64_t D, IoType io, const v
     // full round before it makes up for 110 rows of that, and the launches for
     // kSaved row-steps (steps in whole tiles).  Backward, separate kernels -> this one, us
     // (fp32 layer / bf16 layer / gated):
-    //   rows x steps   taken                                     not taken
+    //   rows x steps   taken                                 not taken
     //   32 x 64        32 -> 27, 30 -> 28, 69 -> 29
-    //   32 x 200       -, -, 78 -> 65                            38 -> 50, 36 -> 41
+    //   32 x 200       -, -, 78 -> 65                        38 -> 50, 36 -> 41
     //   128 x 1024     203 -> 187, 153 -> 144, 308 -> 265
-    //   128 x 8192     -                                         1427 -> 1480, 1049 -> 1114, 2084 -> 2105
+    //   128 x 8192     -                    1427 -> 1480, 1049 -> 1114, 2084 -> 2105
     //   256 x 2048     691 -> 459, 514 -> 338, 1044 -> 612
-    //   257 x 2048     -                                         718 -> 780, 530 -> 594, 1053 -> 1065
+    //   257 x 2048     -                       718 -> 780, 530 -> 594, 1053 -> 1065
     //   300 x 2048     844 -> 795, 624 -> 598, 1237 -> 1088
     const int64_t rows = B % fbw::kMaxGroups, rounds = B / fbw::kMaxGroups;
     const int64_t steps = (L + fbw::TS - 1) / fbw::TS * fbw::TS;

@@ -37,9 +37,12 @@
 #include "launch.hpp"
 #include "lookback.hpp"
 #include "mfma_tile.hpp"
+#include "wave_tile.hpp"
 
 namespace recblr {
 namespace fv2 {
+
+using namespace wtile;
 
 constexpr int TS = 64;             // steps per tile
 constexpr int MB = TS / 32;        // 32-step MFMA blocks per tile
@@ -61,12 +64,8 @@ constexpr int waves() { return 8; }
 template <typename T>
 constexpr int threads() { return waves<T>() * kWave; }
 
-typedef float f16v __attribute__((ext_vector_type(16)));
-typedef __bf16 b8 __attribute__((ext_vector_type(8)));
 typedef __bf16 b4 __attribute__((ext_vector_type(4)));
-typedef float f4 __attribute__((ext_vector_type(4)));
 typedef float f8 __attribute__((ext_vector_type(8)));
-typedef uint32_t u4v __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) void lds_void;
 typedef __attribute__((address_space(1))) void glb_void;
 
@@ -100,11 +99,6 @@ struct Params {
 // differ.
 __device__ __forceinline__ int swz16(int r) { return (r & 7) | ((r >> 1) & 8); }
 __device__ __forceinline__ int swz32(int r) { return ((r >> 3) & 3) << 2; }
-
-// A-operand row of MFMA row R (0..31) in a 32-step block: rows are permuted
-// so that lane half h of the 32 x 32 accumulator holds steps 16 h .. 16 h + 15
-// in VGPRs 0 .. 15 (the accumulator of row 8 (v / 4) + 4 h + v % 4 is VGPR v).
-__device__ __forceinline__ int sigma(int R) { return 16 * ((R >> 2) & 1) + 4 * (R >> 3) + (R & 3); }
 
 template <typename T, int D>
 struct Geo {
@@ -277,32 +271,6 @@ __device__ __forceinline__ void conv_tile(const char* hxb, const float* taps, ch
     }
 }
 
-// v_permlane16_swap of two accumulators: even 16-lane rows keep a and get
-// b's... see the exchange in the kernel.
-__device__ __forceinline__ void swap16(float& a, float& b) {
-    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false,
-                                                    false);
-    a = __uint_as_float(r[0]);
-    b = __uint_as_float(r[1]);
-}
-// The value of the lane in the neighbouring 16-lane row (rows 0 <-> 1, 2 <-> 3).
-__device__ __forceinline__ float row_partner(float v, bool odd) {
-    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false,
-                                                    false);
-    return __uint_as_float(odd ? r[0] : r[1]);
-}
-// The value of the lane 32 away (lower half <-> upper half).
-__device__ __forceinline__ float half_partner(float v, bool upper) {
-    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false,
-                                                    false);
-    return __uint_as_float(upper ? r[0] : r[1]);
-}
-
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const void* p, uint32_t bytes) {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, (int)bytes,
-                                             0x00020000);
-}
-
 __device__ __forceinline__ float silu(float c) { return c * sigmoid(c); }
 
 // gate_forward on pre-activations that still lack their biases: the exponent
@@ -317,20 +285,6 @@ __device__ __forceinline__ void gate_forward_biased(float x, float zr, float zi,
     alpha = fast_exp2(r * cc.neg_s_l2);
     float m = kSeries ? one_minus_exp_neg(r * cc.two_s, alpha) : fmaf(-alpha, alpha, 1.0f);
     u = fast_sqrt(m) * i * x;
-}
-
-// Workgroup barrier for LDS hand-offs that leaves vector-memory operations in
-// flight: __syncthreads() carries a release fence, which waits for every
-// outstanding load and store of the wave (the direct-to-LDS prefetch of the
-// next tile among them).  Here the wave's own LDS writes are waited for
-// (lgkmcnt(0)), and direct-to-LDS loads are waited for explicitly (vmcnt)
-// before the barrier that publishes their data; the empty asm statements keep
-// the compiler from moving memory accesses across the barrier.
-__device__ __forceinline__ void lds_barrier() {
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0); vmcnt and expcnt not waited for
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
 }
 
 // s_waitcnt immediate that waits until at most n vector-memory operations of
@@ -809,8 +763,8 @@ hipError_t launch_fused2_forward(const void* x, const void* wr, const void* br, 
                                  int64_t D, IoType io, void* ws, hipStream_t stream,
                                  const float* conv_w, const float* conv_b, int K) {
     const fv2::Plan pl = fv2::plan(B, L, D, fv2::waves_of(io));
-    fv2::Params P{x,  wr,        wi,  br,  bi,  lambda, h0, h, hT, hz, y, conv_w, conv_b, K, L, D, B * D,
-                  pl.ngroups, pl.nseg, nullptr, nullptr, nullptr};
+    fv2::Params P{x,  wr, wi, br, bi,     lambda, h0, h, hT, hz, y, conv_w, conv_b, K, L, D,
+                  B * D, pl.ngroups, pl.nseg, nullptr, nullptr, nullptr};
     if (pl.lookback) {
         P.status = (unsigned*)((char*)ws + kStatusOffset);
         P.counters = (unsigned*)((char*)ws + 256);

@@ -113,9 +113,9 @@ bool fused_forward_applies(int64_t B, int64_t L, int64_t D, IoType io, const voi
 // Look-back workspace of the fused forward (0 for empty shapes).
 size_t fused_forward_workspace(int64_t B, int64_t L, int64_t D);
 hipError_t launch_fused_forward(const void* x, const void* wr, const void* wi, void* pack,
-                                const void* br, const void* bi, const float* lambda, const float* h0, void* h, float* hT,
-                                int64_t B, int64_t L, int64_t D, IoType io, void* ws,
-                                hipStream_t stream);
+                                const void* br, const void* bi, const float* lambda,
+                                const float* h0, void* h, float* hT, int64_t B, int64_t L,
+                                int64_t D, IoType io, void* ws, hipStream_t stream);
 
 // Scan forward with the gate projections fused in, weights resident in VGPRs
 // (fused_fwd.hip): D = 128 for fp32 I/O, D = 128 or 256 for bf16 I/O, x, W_r
@@ -133,16 +133,11 @@ hipError_t launch_fused2_forward(const void* x, const void* wr, const void* br, 
                                  const float* conv_w = nullptr, const float* conv_b = nullptr,
                                  int K = 0);
 
-// Scan-algorithm variants for the efficiency ablation (zero initial state;
-// x, z, h share the I/O type): a serial scan (one wave per 64 channels walks
-// the sequence) and the two-tree scan over the power of two >= L with the
-// leading positions as identity (embedding padding), L <= 4096.
 // Layer backward's scan with the gate projections recomputed inside
 // (scan_bwd_fused_kernel): x, the weights and room for them packed by channel
 // group and in the order of launch_project_backward_data or (pack_frag)
 // launch_project_backward_both (project_pack_workspace bytes each), biases (may be
-// null); dx in the I/O
-// type, dz_r and dz_i in fp32, [B][L][D].
+// null); dx in the I/O type, dz_r and dz_i in fp32, [B][L][D].
 struct FusedBwdArgs {
     const void* x;
     const void* wr;
@@ -229,6 +224,10 @@ bool fused2_backward_applies(int64_t B, int64_t L, int64_t D, IoType io, const v
 size_t fused2_backward_workspace(int64_t B, int64_t L, int64_t D);
 hipError_t launch_fused2_backward(const Fused2BwdArgs& a, hipStream_t stream);
 
+// Scan-algorithm variants for the efficiency ablation (zero initial state;
+// x, z, h share the I/O type): a serial scan (one wave per 64 channels walks
+// the sequence) and the two-tree scan over the power of two >= L with the
+// leading positions as identity (embedding padding), L <= 4096.
 hipError_t launch_scan_forward_serial(const ScanFwdArgs& a, hipStream_t stream);
 hipError_t launch_scan_forward_tree(const ScanFwdArgs& a, hipStream_t stream);
 bool tree_scan_supported(int64_t L);
@@ -276,9 +275,9 @@ hipError_t launch_conv_backward(const void* hx, const void* dxp, const float* w4
 // The scan forward with the projections fused in (fused_forward_applies) on
 // x = x', storing y = h * SiLU(hz) (and h if not null).
 hipError_t launch_fused_gated_forward(const void* x, const void* hz, const void* wr,
-                                      const void* wi, void* pack, const void* br, const void* bi, const float* lambda,
-                                      const float* h0, void* y, void* h, float* hT, int64_t B,
-                                      int64_t L, int64_t D, IoType io, void* ws,
-                                      hipStream_t stream);
+                                      const void* wi, void* pack, const void* br, const void* bi,
+                                      const float* lambda, const float* h0, void* y, void* h,
+                                      float* hT, int64_t B, int64_t L, int64_t D, IoType io,
+                                      void* ws, hipStream_t stream);
 
 }  // namespace recblr

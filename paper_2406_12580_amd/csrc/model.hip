@@ -380,11 +380,12 @@ __global__ __launch_bounds__(kThreads) void ln_bwd_kernel(
 }
 
 // gamma and beta gradients of every LayerNorm in one launch at the step's end: part is
-// [site][rows][2 D] (from site `compact` on only rows_c of the rows are there), site 0 the embedding's, 1 + 2 l and 2 + 2 l layer l's, whose
-// gradients (gamma, then beta) start at ln1 + l stride and ln2 + l stride.  A workgroup
-// sums 64 columns of a site in double: 16 waves take a range of rows each, 16 loads in
-// flight, and the range sums are added in order.  Each of two sums a site and two stages
-// a sum was a launch of about 5 us (20 in a step of two layers: 110 us; this one 9 us).
+// [site][rows][2 D] (from site `compact` on only rows_c of the rows are there), site 0 the
+// embedding's, 1 + 2 l and 2 + 2 l layer l's, whose gradients (gamma, then beta) start at
+// ln1 + l stride and ln2 + l stride.  A workgroup sums 64 columns of a site in double: 16
+// waves take a range of rows each, 16 loads in flight, and the range sums are added in
+// order.  Each of two sums a site and two stages a sum was a launch of about 5 us (20 in a
+// step of two layers: 110 us; this one 9 us).
 constexpr int kLnWaves = 16;
 __global__ __launch_bounds__(kLnWaves * kWave) void ln_params_kernel(
     const float* __restrict__ part, int64_t rows, int compact, int64_t rows_c, int cols,

@@ -31,20 +31,15 @@
 #include "gemm.hpp"
 #include "launch.hpp"
 #include "mfma_tile.hpp"
+#include "wave_tile.hpp"
 
 namespace recblr {
 namespace pbw {
 
+using namespace wtile;
+
 constexpr int TR = 32;             // rows per tile
 constexpr int NW = 8, NT = NW * kWave;
-
-typedef float f16v __attribute__((ext_vector_type(16)));
-typedef float f4 __attribute__((ext_vector_type(4)));
-typedef __bf16 b8 __attribute__((ext_vector_type(8)));
-typedef short s4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u4v __attribute__((ext_vector_type(4)));
-typedef uint32_t u2v __attribute__((ext_vector_type(2)));
-typedef __attribute__((address_space(3))) s4 lds_s4;
 
 struct Params {
     const float* dzr;
@@ -59,7 +54,8 @@ struct Params {
 
 template <int D>
 struct Geo {
-    static constexpr int CB = D == 256 ? 4 : D == 192 ? 3 : D / 32;  // 32-column blocks of a workgroup
+    // 32-column blocks of a workgroup
+    static constexpr int CB = D == 256 ? 4 : D == 192 ? 3 : D / 32;
     static constexpr int NCB = D / (32 * CB);                        // column blocks
     static constexpr int OB = 2 * D / 32;                            // 32-row blocks of dW
     static constexpr int PO = (OB + NW - 1) / NW;                    // of a wave
@@ -81,32 +77,6 @@ struct Geo {
 // fragment read land on distinct chunks, the four rows x 64 bytes of a
 // transposing read in distinct 64-byte groups.
 __device__ __forceinline__ int swz(int r) { return ((r & 3) << 2) | ((r >> 2) & 3); }
-
-__device__ __forceinline__ void lds_barrier() {
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0); vector memory stays in flight
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-}
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const void* p, uint32_t bytes) {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, (int)bytes,
-                                             0x00020000);
-}
-__device__ __forceinline__ int fresh(int lane) {
-    asm volatile("" : "+v"(lane));  // addresses are formed again in each tile, not kept
-    return lane;
-}
-__device__ __forceinline__ b8 tr_pair(const char* p0, const char* p1) {
-    const s4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4*)p0);
-    const s4 c = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4*)p1);
-    return __builtin_bit_cast(b8, __builtin_shufflevector(a, c, 0, 1, 2, 3, 4, 5, 6, 7));
-}
-template <int PA, int PB>
-__device__ __forceinline__ f16v mma(const b8 (&a)[PA], const b8 (&b)[PB], f16v acc) {
-    if constexpr (PB == 2) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], b[1], acc, 0, 0, 0);
-    if constexpr (PA == 2) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[1], b[0], acc, 0, 0, 0);
-    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], b[0], acc, 0, 0, 0);
-}
 
 template <typename TX, typename TW, typename TD, int D>
 __global__ __launch_bounds__(NT, 2) void dxdw_kernel(Params P) {
@@ -182,7 +152,8 @@ __global__ __launch_bounds__(NT, 2) void dxdw_kernel(Params P) {
             constexpr int cpr = 32 * G::CB * EX / 16;
             const int r = o / cpr, c = o % cpr;
             xq[q] = __builtin_amdgcn_raw_buffer_load_b128(
-                rx, o < kXq ? (uint32_t)((r * D + cb * 32 * G::CB) * EX + c * 16) : 0x7FFFFFFFu, 0, 0);
+                rx, o < kXq ? (uint32_t)((r * D + cb * 32 * G::CB) * EX + c * 16) : 0x7FFFFFFFu, 0,
+                0);
         }
     };
     auto stage_dz = [&](char* dzp) {
@@ -472,7 +443,8 @@ bool takes(int64_t M, int64_t D, IoType x_io) {
 bool project_backward_both_applies(int64_t M, int64_t D, IoType x_io, const void* dzr,
                                    const void* dzi, const void* x, const void* dx,
                                    const void* ws) {
-    const uintptr_t a = (uintptr_t)dzr | (uintptr_t)dzi | (uintptr_t)x | (uintptr_t)dx | (uintptr_t)ws;
+    const uintptr_t a =
+        (uintptr_t)dzr | (uintptr_t)dzi | (uintptr_t)x | (uintptr_t)dx | (uintptr_t)ws;
     return pbw::takes(M, D, x_io) && a % 16 == 0;  // 16-byte loads and stores
 }
 

@@ -674,18 +674,18 @@ static hipError_t launch_fused_t(const void* x, const void* wr, const void* wi, 
 }
 
 hipError_t launch_fused_forward(const void* x, const void* wr, const void* wi, void* pack,
-                                const void* br, const void* bi, const float* lambda, const float* h0, void* h, float* hT,
-                                int64_t B, int64_t L, int64_t D, IoType io, void* ws,
-                                hipStream_t stream) {
+                                const void* br, const void* bi, const float* lambda,
+                                const float* h0, void* h, float* hT, int64_t B, int64_t L,
+                                int64_t D, IoType io, void* ws, hipStream_t stream) {
     return launch_fused_t<false>(x, wr, wi, pack, br, bi, lambda, h0, h, hT, B, L, D, io, ws,
                                  fusedfwd::GatedArgs{}, stream);
 }
 
 hipError_t launch_fused_gated_forward(const void* x, const void* hz, const void* wr,
-                                      const void* wi, void* pack, const void* br, const void* bi, const float* lambda,
-                                      const float* h0, void* y, void* h, float* hT, int64_t B,
-                                      int64_t L, int64_t D, IoType io, void* ws,
-                                      hipStream_t stream) {
+                                      const void* wi, void* pack, const void* br, const void* bi,
+                                      const float* lambda, const float* h0, void* y, void* h,
+                                      float* hT, int64_t B, int64_t L, int64_t D, IoType io,
+                                      void* ws, hipStream_t stream) {
     return launch_fused_t<true>(x, wr, wi, pack, br, bi, lambda, h0, h, hT, B, L, D, io, ws,
                                 fusedfwd::GatedArgs{hz, y}, stream);
 }

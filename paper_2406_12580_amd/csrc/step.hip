@@ -334,9 +334,9 @@ hipError_t launch_ks(const void* x, const void* wr, const void* br, const void* 
 // once, multiplies them (v_mfma_f32_16x16x32_bf16; fp32 operands as the 3-term
 // split hi*hi + hi*lo + lo*hi), and the waves' partial z meet in LDS, added in
 // wave order.  8 rows at D = 256: 2.6 us (bf16; 10.4 us with the weights loaded
-// whole by one workgroup) and 3.2 us (fp32; 16 us with a packing launch).  Then one thread per (row, channel) takes the step; its h_prev, x
-// and constants were loaded before the products.  Row blocks of 16: blockIdx.y,
-// + gridDim.y, ...
+// whole by one workgroup) and 3.2 us (fp32; 16 us with a packing launch).  Then
+// one thread per (row, channel) takes the step; its h_prev, x and constants were
+// loaded before the products.  Row blocks of 16: blockIdx.y, + gridDim.y, ...
 namespace few {
 
 typedef __bf16 b8 __attribute__((ext_vector_type(8)));
