@@ -767,12 +767,6 @@ constexpr int kInBwdSmem = 2 * 2 * kPlane + NW * 3 * kTrans + kExch;
 constexpr int kFwdSmem = 2 * 3 * kPlane + 2 * kExch;
 constexpr int kBwdSmem = 2 * 5 * kPlane + NW * 3 * kTrans + kExch;
 
-template <typename K>
-hipError_t allow_lds(K kern, int bytes) {
-    return hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
-                               bytes);
-}
-
 // `most` workgroups (one or two per compute unit), a tile or more each: every range
 // leaves a partial of its weight gradients to sum, but few rows in few ranges leave the
 // chip idle (model step of 2000 rows, two layers: 437 us with at least 256 rows a range,
@@ -815,8 +809,9 @@ size_t sublayers_fused_colsum(int64_t M) {
 
 hipError_t launch_ffn_forward(const float* x, const float* w1, const float* b1, const float* w2,
                               const float* b2, float* a, float* q, int64_t M, hipStream_t stream) {
-    static const hipError_t attr = ffn::allow_lds(ffn::ffn_fwd_kernel, ffn::kFwdSmem);
-    if (attr != hipSuccess) return attr;
+    static std::atomic<uint64_t> lds_set{0};
+    hipError_t e = allow_dynamic_lds((const void*)ffn::ffn_fwd_kernel, ffn::kFwdSmem, lds_set);
+    if (e != hipSuccess) return e;
     const int64_t tiles = (M + ffn::TR - 1) / ffn::TR;
     const dim3 grid((unsigned)(tiles < 256 ? tiles : 256));
     hipLaunchKernelGGL(ffn::ffn_fwd_kernel, grid, dim3(ffn::NT), ffn::kFwdSmem, stream,
@@ -827,13 +822,14 @@ hipError_t launch_ffn_forward(const float* x, const float* w1, const float* b1, 
 hipError_t launch_ffn_backward(const float* x, const float* dq, const float* a, const float* w1,
                                const float* w2, float* dx, float* grads, int64_t M, float* part,
                                void* colsum_ws, hipStream_t stream) {
-    static const hipError_t attr = ffn::allow_lds(ffn::ffn_bwd_kernel, ffn::kBwdSmem);
-    if (attr != hipSuccess) return attr;
+    static std::atomic<uint64_t> lds_set{0};
+    hipError_t e = allow_dynamic_lds((const void*)ffn::ffn_bwd_kernel, ffn::kBwdSmem, lds_set);
+    if (e != hipSuccess) return e;
     int64_t ranges, rows;
     ffn::split(M, 256, &ranges, &rows);
     hipLaunchKernelGGL(ffn::ffn_bwd_kernel, dim3((unsigned)ranges), dim3(ffn::NT), ffn::kBwdSmem,
                        stream, ffn::BwdParams{x, dq, a, w1, w2, dx, part, M, ranges, rows});
-    const hipError_t e = hipGetLastError();
+    e = hipGetLastError();
     if (e != hipSuccess) return e;
     return launch_colsum(part, ranges, ffn::kPart, grads, colsum_ws, stream);
 }
@@ -851,14 +847,16 @@ hipError_t launch_proj_in_forward(const float* x, const float* wx, const float* 
 hipError_t launch_proj_in_backward(const float* x, const float* dhx, const float* dhz,
                                    const float* wx, const float* wz, float* dx, float* grads,
                                    int64_t M, float* part, void* colsum_ws, hipStream_t stream) {
-    static const hipError_t attr = ffn::allow_lds(ffn::proj_in_bwd_kernel, ffn::kInBwdSmem);
-    if (attr != hipSuccess) return attr;
+    static std::atomic<uint64_t> lds_set{0};
+    hipError_t e =
+        allow_dynamic_lds((const void*)ffn::proj_in_bwd_kernel, ffn::kInBwdSmem, lds_set);
+    if (e != hipSuccess) return e;
     int64_t ranges, rows;
     ffn::split(M, 256, &ranges, &rows);
     hipLaunchKernelGGL(ffn::proj_in_bwd_kernel, dim3((unsigned)ranges), dim3(ffn::NT),
                        ffn::kInBwdSmem, stream,
                        ffn::InBwdParams{x, dhx, dhz, wx, wz, dx, part, M, ranges, rows});
-    const hipError_t e = hipGetLastError();
+    e = hipGetLastError();
     if (e != hipSuccess) return e;
     return launch_colsum(part, ranges, ffn::kInPart, grads, colsum_ws, stream);
 }

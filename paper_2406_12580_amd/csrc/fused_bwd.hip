@@ -866,9 +866,9 @@ template <typename TX, typename TH, typename TW, bool GATE>
 hipError_t launch(const Params& P, int grid, hipStream_t stream) {
     auto kern = fused_bwd_kernel<TX, TH, TW, GATE>;
     constexpr int smem = Geo<TX, TW, GATE>::kSmem;
-    static const hipError_t attr =
-        hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, smem);
-    if (attr != hipSuccess) return attr;
+    static std::atomic<uint64_t> lds_set{0};
+    const hipError_t e = allow_dynamic_lds((const void*)kern, smem, lds_set);
+    if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(NT), smem, stream, P);
     return hipGetLastError();
 }

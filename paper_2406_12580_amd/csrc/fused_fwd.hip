@@ -717,9 +717,9 @@ template <typename T, int D, bool GATED, bool LOOKBACK, bool CONV>
 hipError_t launch(const Params& P, int grid, hipStream_t stream) {
     auto kern = fused_fwd_kernel<T, D, GATED, LOOKBACK, CONV>;
     constexpr int smem = CONV ? ConvGeo<T, D>::kSmem : Geo<T, D>::kSmem, nt = Geo<T, D>::NT;
-    static const hipError_t attr =
-        hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, smem);
-    if (attr != hipSuccess) return attr;
+    static std::atomic<uint64_t> lds_set{0};
+    const hipError_t e = allow_dynamic_lds((const void*)kern, smem, lds_set);
+    if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(nt), smem, stream, P);
     return hipGetLastError();
 }

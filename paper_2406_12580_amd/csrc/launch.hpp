@@ -8,6 +8,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <atomic>
+
 namespace recblr {
 
 enum class IoType : int { kF32 = 0, kBf16 = 1 };
@@ -65,6 +67,20 @@ inline hipError_t launch_measured(Kernel kernel, dim3 grid, dim3 block, hipStrea
     else
         hipLaunchKernelGGL(kernel, grid, block, 0, stream, args...);
     return hipGetLastError();
+}
+
+// Lets a kernel take more than 64 KB of dynamic LDS, once per device it runs on: the
+// attribute belongs to the kernel as loaded on the current device.  done: a static of the
+// caller's for this kernel, a bit per device (devices past 63 set it on each launch).
+inline hipError_t allow_dynamic_lds(const void* kernel, int bytes, std::atomic<uint64_t>& done) {
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    const uint64_t bit = dev >= 0 && dev < 64 ? (uint64_t)1 << dev : 0;
+    if (done.load(std::memory_order_acquire) & bit) return hipSuccess;
+    e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+    if (e == hipSuccess) done.fetch_or(bit, std::memory_order_release);
+    return e;
 }
 
 // Static scratch of the entry point that allocates nothing

@@ -399,9 +399,9 @@ template <typename TX, typename TW, typename TD, int D>
 hipError_t launch_d(const Params& P, hipStream_t stream) {
     auto kern = dxdw_kernel<TX, TW, TD, D>;
     constexpr int smem = (int)Geo<D>::smem(sizeof(TX) == 4 ? 2 : 1);
-    static const hipError_t attr =
-        hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, smem);
-    if (attr != hipSuccess) return attr;
+    static std::atomic<uint64_t> lds_set{0};
+    const hipError_t e = allow_dynamic_lds((const void*)kern, smem, lds_set);
+    if (e != hipSuccess) return e;
     const unsigned grid = (unsigned)((P.ranges + 7) / 8 * 8 * Geo<D>::NCB);
     hipLaunchKernelGGL(kern, dim3(grid), dim3(NT), smem, stream, P);
     return hipGetLastError();

@@ -866,3 +866,20 @@ def test_workspace_status_word(rb, shape, io):
     assert int(wsb[4:8].view(torch.int32).item()) == 0
     if nf:
         assert int(wsf[4:8].view(torch.int32).item()) == 0
+
+
+def test_second_device(rb):
+    """Kernels with more LDS than the default limit, on a second GPU after the first."""
+    import torch
+    if torch.cuda.device_count() < 2:
+        pytest.skip("one GPU")
+    for D in (128, 192):
+        f = dg.full_inputs(3, 40, D, 6200 + D, bias=True, grad=True)
+        want = oracle.backward(f.x, f.Wr, f.br, f.Wi, f.bi, f.lam, f.dh)
+        for n in (0, 1):
+            with torch.cuda.device(n):
+                args = [dev(a) for a in (f.x, f.Wr, f.br, f.Wi, f.bi)] + [dev32(f.lam)]
+                h, _ = rb.bdlru_forward(*args)
+                got = rb.bdlru_backward(*args, h, dev(f.dh))
+                for k in ("dx", "dWr", "dbr", "dWi", "dbi", "dlambda"):
+                    assert_close(host(got[k]), want[k], "f32", k)
