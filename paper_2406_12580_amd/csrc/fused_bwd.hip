@@ -588,6 +588,10 @@ __global__ __launch_bounds__(NT, 2) void fused_bwd_kernel(Params P) {
                     if (m == 1) nx[k] = n;
                     else later[k] = n;
                 }
+                if (m == 0) {  // ahead of the last stores (behind them: 2048 x 200 530 -> 547 us)
+                    dcb = sb;  // joins `total` with the next tile's sums
+                    total_w += (double)row_sums(sw[0], sw[1], sw[2], sw[3]);
+                }
                 const uint32_t off = (uint32_t)((t0 + 32 * m + 8 * rho) * D + ch) * EX;
 #pragma unroll
                 for (int i = 0; i < 8; ++i)
@@ -596,8 +600,6 @@ __global__ __launch_bounds__(NT, 2) void fused_bwd_kernel(Params P) {
                                                        fmaf(wt[2], dc[i + 2], wt[3] * dc[i + 3]))));
             }
             wave_fence();  // stage() overwrites the steps that other lanes read here
-            dcb = sb;  // joins `total` with the next tile's sums
-            total_w += (double)row_sums(sw[0], sw[1], sw[2], sw[3]);
         }
     };
 
